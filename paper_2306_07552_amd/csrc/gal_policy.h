@@ -11,6 +11,7 @@ constexpr int kPolicyRes = 128;      // depth image edge the encoder takes
 constexpr int kPolicyFeat = 512;     // encoder features
 constexpr int kPolicyProprio = 7;    // joint angles fed to the heads beside the features
 constexpr int kPolicyMaxAct = 32;    // action dimensions
+constexpr int kPolicyCUs = 256;      // compute units of the chip: workgroups of the persistent kernels
 
 // One convolution as an implicit GEMM over NHWC input: `rows` = envs x oh x
 // ow output pixels, `k` = kw x kw x in_c, `out_c` output channels.
@@ -20,8 +21,15 @@ struct ConvGeom {
     int oh, ow, kw, stride;
 };
 
-hipError_t conv_gemm(bool depth_input, const void *in, const uint16_t *W, const float *bias, const ConvGeom &g,
-                     uint16_t *out, hipStream_t s);
+// The three convolutions of the encoder on n depth images: BF16 weights in the
+// parameter layout (rows of (ky, kx, channel)), FP32 biases; NHWC BF16 maps of
+// each layer out.
+struct EncoderWeights {
+    const uint16_t *w1, *w2, *w3;
+    const float *b1, *b2, *b3;
+};
+hipError_t encoder_forward(const uint32_t *depth, const EncoderWeights &w, int n, uint16_t *h1, uint16_t *h2,
+                           uint16_t *h3, hipStream_t s);
 hipError_t policy_heads(const uint16_t *h, const float *state, const float *aw, const float *ab, const float *vw,
                         const float *vb, const float *log_std, int A, int n_envs, const float *noise,
                         float *actions, float *value, float *logp, hipStream_t s);

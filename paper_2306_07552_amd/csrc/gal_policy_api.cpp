@@ -210,11 +210,9 @@ gal::ConvGeom geom(const gal_policy *p, int l, int n)
 // the encoder on n images: h[0..3]
 int encode(gal_policy *p, const uint32_t *depth_dev, int n, hipStream_t s)
 {
-    const void *in = depth_dev;
-    for (int l = 0; l < 3; ++l) {
-        POL_TRY(gal::conv_gemm(l == 0, in, p->wb + p->off_w[l], p->w + p->off_b[l], geom(p, l, n), p->h[l], s));
-        in = p->h[l];
-    }
+    const gal::EncoderWeights w = {p->wb + p->off_w[0], p->wb + p->off_w[1], p->wb + p->off_w[2],
+                                   p->w + p->off_b[0],  p->w + p->off_b[1],  p->w + p->off_b[2]};
+    POL_TRY(gal::encoder_forward(depth_dev, w, n, p->h[0], p->h[1], p->h[2], s));
     const int flat = p->side[3] * p->side[3] * kConv[2][0];
     POL_TRY(gal::fc_forward(p->h[2], p->wb + p->off_w[3], p->w + p->off_b[3], n, gal::kPolicyFeat, flat, p->fc_ws,
                             p->fc_ws_floats, p->h[3], s));
