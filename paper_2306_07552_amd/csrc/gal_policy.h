@@ -13,14 +13,6 @@ constexpr int kPolicyProprio = 7;    // joint angles fed to the heads beside the
 constexpr int kPolicyMaxAct = 32;    // action dimensions
 constexpr int kPolicyCUs = 256;      // compute units of the chip: workgroups of the persistent kernels
 
-// One convolution as an implicit GEMM over NHWC input: `rows` = envs x oh x
-// ow output pixels, `k` = kw x kw x in_c, `out_c` output channels.
-struct ConvGeom {
-    int rows, out_c, k;
-    int ih, iw, in_c;
-    int oh, ow, kw, stride;
-};
-
 // The three convolutions of the encoder on n depth images: BF16 weights in the
 // parameter layout (rows of (ky, kx, channel)), FP32 biases; NHWC BF16 maps of
 // each layer out.
@@ -42,18 +34,22 @@ int fc_splits(int rows, int N, int K);
 hipError_t fc_forward(const uint16_t *x, const uint16_t *W, const float *bias, int rows, int N, int K, float *ws,
                       size_t ws_floats, uint16_t *out, hipStream_t s);
 
-// Backward: weight gradient of a convolution into out [out_c][k] and its
-// bias gradient into bias_out [out_c] (FP32, split over the output pixels
-// into `part`, then summed in split order); the input gradient (adjoint)
-// masked by the ReLU of h (the layer's input activation), through
-// Wt [in_c][taps x out_c] (scratch, rebuilt here).
-hipError_t conv_dw(bool depth_input, const void *in, const uint16_t *dy, const ConvGeom &g, float *part,
-                   size_t part_floats, float *out, float *bias_out, hipStream_t s);
+// Backward of the three convolutions from d3 (the gradient of the third's
+// pre-activation, BF16 [n][12][12][32]): the FP32 gradients of conv1 W, b,
+// conv2 W, b into g12 and of conv3 W, b into g3 (parameter layout).  d2 (BF16
+// [n][14][14][64]) receives the second layer's gradient; wt
+// (encoder_backward_weights() BF16 values) and part (encoder_backward_floats())
+// are scratch.
+size_t encoder_backward_floats();
+size_t encoder_backward_weights();
+hipError_t encoder_backward(const uint32_t *depth, const uint16_t *h1, const uint16_t *h2, const uint16_t *d3,
+                            uint16_t *d2, const uint16_t *w2, const uint16_t *w3, uint16_t *wt, int n, float *part,
+                            size_t part_floats, float *g12, float *g3, hipStream_t s);
+// out[i] = sum over splits of part[z][i] (FP32, n values each) in a fixed order.
+hipError_t sum_parts(const float *part, int splits, int64_t n, float *out, hipStream_t s);
 // Column sums of a BF16 [rows][D] matrix (bias gradients), chunked through
 // part and summed in chunk order (deterministic).
 hipError_t colsum(const uint16_t *g, int rows, int D, float *part, size_t part_floats, float *out, hipStream_t s);
-hipError_t conv_dx(const uint16_t *dy, const uint16_t *W, uint16_t *Wt, const uint16_t *h, const ConvGeom &g,
-                   uint16_t *dx, hipStream_t s);
 hipError_t ppo_heads(const uint16_t *h, const float *state, const float *aw, const float *ab, const float *vw,
                      const float *vb, const float *log_std, int A, int S, const float *actions, const float *old_logp,
                      const float *adv, const float *ret, float clip, float vcoef, float *gm, float *gls, float *gv,

@@ -46,7 +46,7 @@ struct gal_policy {
     int32_t last_envs = 0;
     // training (allocated on the first update)
     float *g = nullptr, *m = nullptr, *v = nullptr;          // gradient, Adam moments
-    uint16_t *d[4] = {nullptr, nullptr, nullptr, nullptr};   // gradients of the pre-activations of conv1..3, fc
+    uint16_t *d[4] = {nullptr, nullptr, nullptr, nullptr};   // gradients of the pre-activations of conv2, conv3, fc
     uint16_t *wt = nullptr;                                  // adjoint weights
     float *gm = nullptr, *gls = nullptr, *gv = nullptr, *terms = nullptr;
     float *part = nullptr;
@@ -193,20 +193,6 @@ int gal_policy_get_weights(gal_policy *p, float *host, size_t count)
 
 namespace {
 
-gal::ConvGeom geom(const gal_policy *p, int l, int n)
-{
-    gal::ConvGeom g;
-    g.ih = g.iw = p->side[l];
-    g.in_c = kConv[l][3];
-    g.kw = kConv[l][1];
-    g.stride = kConv[l][2];
-    g.oh = g.ow = p->side[l + 1];
-    g.out_c = kConv[l][0];
-    g.k = g.kw * g.kw * g.in_c;
-    g.rows = n * g.oh * g.ow;
-    return g;
-}
-
 // the encoder on n images: h[0..3]
 int encode(gal_policy *p, const uint32_t *depth_dev, int n, hipStream_t s)
 {
@@ -224,16 +210,16 @@ int train_buffers(gal_policy *p)
     if (p->g) return GAL_OK;
     const int n = p->max_envs, A = p->A;
     const int flat = p->side[3] * p->side[3] * kConv[2][0];
-    // split-K workspace: the fc weight gradient's (<= 16 splits) or a convolution's (<= 256 splits)
-    p->part_floats = std::max<size_t>((size_t)16 * gal::kPolicyFeat * flat, (size_t)256 * 64 * 16 * 32);
+    // workspace: the fc weight gradient's splits (<= 16) or the convolutions' slabs
+    p->part_floats = std::max<size_t>((size_t)16 * gal::kPolicyFeat * flat, gal::encoder_backward_floats());
     int rc;
     if ((rc = p->alloc(&p->g, p->n_params)) || (rc = p->alloc(&p->m, p->n_params)) ||
-        (rc = p->alloc(&p->v, p->n_params)) || (rc = p->alloc(&p->wt, (size_t)64 * 16 * 32)) ||
+        (rc = p->alloc(&p->v, p->n_params)) || (rc = p->alloc(&p->wt, gal::encoder_backward_weights())) ||
         (rc = p->alloc(&p->gm, (size_t)n * A)) || (rc = p->alloc(&p->gls, (size_t)n * A)) ||
         (rc = p->alloc(&p->gv, (size_t)n)) || (rc = p->alloc(&p->terms, (size_t)n * 3)) ||
         (rc = p->alloc(&p->part, p->part_floats)))
         return rc;
-    for (int l = 0; l < 4; ++l)
+    for (int l = 1; l < 4; ++l)   // conv1's stays on the chip
         if ((rc = p->alloc(&p->d[l], p->act_count(l, n)))) return rc;
     POL_TRY(hipMemset(p->m, 0, sizeof(float) * p->n_params));
     POL_TRY(hipMemset(p->v, 0, sizeof(float) * p->n_params));
@@ -296,14 +282,10 @@ int gal_policy_ppo_gradients(gal_policy *p, const uint32_t *depth_dev, const flo
     POL_TRY(gal::colsum(p->d[3], S, gal::kPolicyFeat, p->part, p->part_floats, g + p->off_b[3], s));
     POL_TRY(gal::mlp_gemm(gal::kGemmDx, p->d[3], p->wb + p->off_w[3], S, flat, gal::kPolicyFeat, gal::kPolicyFeat,
                           flat, nullptr, p->h[2], flat, nullptr, p->d[2], flat, s));
-    // convolutions 3, 2, 1
-    for (int l = 2; l >= 0; --l) {
-        const gal::ConvGeom gg = geom(p, l, S);
-        const void *in = l == 0 ? (const void *)depth_dev : (const void *)p->h[l - 1];
-        POL_TRY(gal::conv_dw(l == 0, in, p->d[l], gg, p->part, p->part_floats, g + p->off_w[l], g + p->off_b[l], s));
-        if (l > 0)
-            POL_TRY(gal::conv_dx(p->d[l], p->wb + p->off_w[l], p->wt, p->h[l - 1], gg, p->d[l - 1], s));
-    }
+    // convolutions 3, 2, 1 (conv1's and conv2's parameters follow each other, and conv3's)
+    POL_TRY(gal::encoder_backward(depth_dev, p->h[0], p->h[1], p->d[2], p->d[1], p->wb + p->off_w[1],
+                                  p->wb + p->off_w[2], p->wt, S, p->part, p->part_floats, g + p->off_w[0],
+                                  g + p->off_w[2], s));
     if (grads_dev)
         POL_TRY(hipMemcpyAsync(grads_dev, g, sizeof(float) * p->n_params, hipMemcpyDeviceToDevice, s));
     return GAL_OK;

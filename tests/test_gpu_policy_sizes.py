@@ -34,3 +34,41 @@ def test_policy_batch_sizes(n):
     envs = np.unique(np.array([0, n // 3, n // 2, min(255, n - 1), min(256, n - 1), n - 1]))
     check_policy(pol, theta, np.minimum(depth[envs], 0xFFFFFF), state[envs], noise[envs].astype(np.float64),
                  act.cpu().numpy()[envs], val.cpu().numpy()[envs], lp.cpu().numpy()[envs], envs)
+
+
+@pytest.mark.parametrize("S", [16, 256, 512, 1024])
+def test_ppo_gradient_is_the_mean_of_its_samples(S):
+    """The gradient over S samples drawn from 16 different ones is the mean of
+    the 16 one-sample gradients, weighted by their counts: one sample per
+    workgroup, fewer, and loops of two and four.  1 / S is a power of two, so
+    every BF16 value is an exact multiple of the one-sample call's and only the
+    FP32 sums differ: over up to 2^20 terms of random sign their rounding grows as
+    2^10 2^-24 of the terms' root sum of squares, and 1e-3 relative L2 leaves 16
+    times that for cancellation."""
+    import torch
+    from oracle import oracle_policy as OP
+    from test_gpu_ppo import ppo_case
+    print("case: ppo gradients as a mean", S, flush=True)
+    from paper_2306_07552_amd import gal
+    small, _, _, _, (out, act, old, adv, ret) = ppo_case(torch, 16, 36)
+    pol = gal.Policy(S, act_dim=9)
+    pol.set_weights(small.get_weights())
+    depth = out["depth"].reshape(16, -1)
+    old, adv, ret = (torch.from_numpy(x).cuda() for x in (old, adv, ret))
+    g = torch.empty(pol.num_params, device="cuda")
+    one = np.zeros((16, pol.num_params))
+    for k in range(16):
+        pol.ppo_gradients(depth[k].contiguous(), out["state"][k:k + 1].contiguous(), act[k:k + 1].contiguous(),
+                          old[k:k + 1], adv[k:k + 1], ret[k:k + 1], grads=g)
+        one[k] = g.cpu().numpy()
+    idx = np.random.default_rng(S).integers(0, 16, size=S)
+    i = torch.from_numpy(idx).cuda()
+    pol.ppo_gradients(depth[i].contiguous(), out["state"][i].contiguous(), act[i].contiguous(), old[i].contiguous(),
+                      adv[i].contiguous(), ret[i].contiguous(), grads=g)
+    got, ref = g.cpu().numpy().astype(np.float64), one[idx].mean(axis=0)
+    off = 0
+    for name, shp in OP.layout(9):
+        n = int(np.prod(shp))
+        a, b = got[off:off + n], ref[off:off + n]
+        assert np.linalg.norm(a - b) <= 1e-3 * max(np.linalg.norm(b), 1e-30), name
+        off += n
