@@ -28,6 +28,14 @@ constexpr int kMaxDwSplits = 16;
 // K (in 32-column steps) into part + z M N, FP32 [M][N]; no reduction.
 hipError_t mlp_gemm_parts(const uint16_t *A, const uint16_t *B, int M, int N, int K, int lda, int ldb, int splits,
                           float *part, hipStream_t s);
+// The tiled GEMM behind the variants (k_gemm.hip), for 16-byte aligned rows:
+// whether it takes these operands (A, B: k-strided or not), and its launch.
+// With splits > 1 the FP32 variants write one [M][ldc] slab per split of K.
+bool gemm_tiles_fit(bool strided_a, bool strided_b, const uint16_t *A, const uint16_t *B, int M, int N, int K, int lda,
+                    int ldb, const void *bias, const void *mask, int ldm, const void *C, int ldc);
+hipError_t gemm_tiles(int variant, const uint16_t *A, const uint16_t *B, int M, int N, int K, int lda, int ldb,
+                      const float *bias, const uint16_t *mask, int ldm, float *Cf, uint16_t *Cb, int ldc, int splits,
+                      hipStream_t s);
 hipError_t mlp_gemm(int variant, const uint16_t *A, const uint16_t *B, int M, int N, int K, int lda,
                     int ldb, const float *bias, const uint16_t *mask, int ldm, float *Cf,
                     uint16_t *Cb, int ldc, hipStream_t s, float *ws = nullptr, size_t ws_floats = 0);

@@ -15,6 +15,8 @@
 #include "gal_internal.h"
 #include "gal_mlp.h"
 
+#include <algorithm>
+
 namespace gal {
 
 namespace {
@@ -289,6 +291,26 @@ hipError_t mlp_gemm(int variant, const uint16_t *A, const uint16_t *B, int M, in
                     uint16_t *Cb, int ldc, hipStream_t s, float *ws, size_t ws_floats)
 {
     if (M <= 0 || N <= 0) return hipSuccess;
+    const bool sa = variant == kGemmDw || variant == kGemmTnF32;
+    const bool sb = sa || variant == kGemmDx || variant == kGemmNnF32;
+    if (gemm_tiles_fit(sa, sb, A, B, M, N, K, lda, ldb, bias, mask, ldm, Cf ? (const void *)Cf : (const void *)Cb, ldc)) {
+        int splits = 1;
+        if (variant == kGemmDw && ws && ldc == N) {
+            // aim at 512 workgroups (two per CU) of at least 256 rows: of 128 x 128
+            // tiles where those are many, else of 64 x 64
+            const int t64 = ((N + 63) / 64) * ((M + 63) / 64), t128 = ((N + 127) / 128) * ((M + 127) / 128);
+            splits = std::min(512 / (t128 >= 64 ? t128 : t64), K / 256);
+            splits = (int)std::min<int64_t>(splits, (int64_t)(ws_floats / ((size_t)M * N)));
+            splits = std::max(1, std::min(splits, kMaxDwSplits));
+        }
+        if (splits == 1)
+            return gemm_tiles(variant, A, B, M, N, K, lda, ldb, bias, mask, ldm, Cf, Cb, ldc, 1, s);
+        hipError_t e = gemm_tiles(variant, A, B, M, N, K, lda, ldb, nullptr, nullptr, 0, ws, nullptr, N, splits, s);
+        if (e != hipSuccess) return e;
+        const int64_t n = (int64_t)M * N;
+        hipLaunchKernelGGL(k_sum_splits, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, ws, splits, n, Cf);
+        return hipGetLastError();
+    }
     switch (variant) {
     case kGemmFwd:    // Y = X W^T (+ b, ReLU, BF16)
         return gemm<false, true, kEpiBiasReluBf16>(A, B, M, N, K, lda, ldb, bias, mask, ldm, Cf, Cb, ldc, s);
@@ -324,6 +346,8 @@ hipError_t mlp_gemm_parts(const uint16_t *A, const uint16_t *B, int M, int N, in
 {
     if (M <= 0 || N <= 0) return hipSuccess;
     if (splits < 1 || !part) return hipErrorInvalidValue;
+    if (gemm_tiles_fit(false, false, A, B, M, N, K, lda, ldb, nullptr, nullptr, 0, part, N))
+        return gemm_tiles(kGemmNtF32, A, B, M, N, K, lda, ldb, nullptr, nullptr, 0, part, nullptr, N, splits, s);
     const dim3 grid((N + kBN - 1) / kBN, (M + kBM - 1) / kBM, splits);
     hipLaunchKernelGGL((k_gemm<false, true, kEpiF32>), grid, dim3(256), 0, s, A, B, M, N, K, lda, ldb, nullptr,
                        nullptr, 0, part, nullptr, N);
