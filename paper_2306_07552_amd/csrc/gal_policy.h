@@ -22,17 +22,25 @@ struct EncoderWeights {
 };
 hipError_t encoder_forward(const uint32_t *depth, const EncoderWeights &w, int n, uint16_t *h1, uint16_t *h2,
                            uint16_t *h3, hipStream_t s);
-hipError_t policy_heads(const uint16_t *h, const float *state, const float *aw, const float *ab, const float *vw,
-                        const float *vb, const float *log_std, int A, int n_envs, const float *noise,
-                        float *actions, float *value, float *logp, hipStream_t s);
 
 // The fully connected layer Y = bf16(relu(X W^T + b)) (X [rows][K], W [N][K]):
-// split over K into ws when the tiles alone leave the chip idle (the splits
-// are added in order), else one pass with the bias and ReLU fused.  The
-// workspace needed: at most fc_splits(rows, N, K) * rows * N floats.
+// one pass, or split over K into ws when the tiles alone leave the chip idle;
+// the heads then add the splits in order (`parts`: splits slabs of `stride`
+// values, splits 1 = Y is already in out).  The workspace needed: at most
+// fc_splits(rows, N, K) * rows * N floats.
+struct FcParts {
+    const float *part;
+    int splits;
+    int64_t stride;
+    const float *bias;
+};
 int fc_splits(int rows, int N, int K);
 hipError_t fc_forward(const uint16_t *x, const uint16_t *W, const float *bias, int rows, int N, int K, float *ws,
-                      size_t ws_floats, uint16_t *out, hipStream_t s);
+                      size_t ws_floats, uint16_t *out, FcParts *parts, hipStream_t s);
+// The heads on the features h (written from fc first where it holds splits).
+hipError_t policy_heads(const FcParts &fc, uint16_t *h, const float *state, const float *aw, const float *ab,
+                        const float *vw, const float *vb, const float *log_std, int A, int n_envs, const float *noise,
+                        float *actions, float *value, float *logp, hipStream_t s);
 
 // Backward of the three convolutions from d3 (the gradient of the third's
 // pre-activation, BF16 [n][12][12][32]): the FP32 gradients of conv1 W, b,
@@ -47,18 +55,19 @@ hipError_t encoder_backward(const uint32_t *depth, const uint16_t *h1, const uin
                             size_t part_floats, float *g12, float *g3, hipStream_t s);
 // out[i] = sum over splits of part[z][i] (FP32, n values each) in a fixed order.
 hipError_t sum_parts(const float *part, int splits, int64_t n, float *out, hipStream_t s);
-// Column sums of a BF16 [rows][D] matrix (bias gradients), chunked through
-// part and summed in chunk order (deterministic).
-hipError_t colsum(const uint16_t *g, int rows, int D, float *part, size_t part_floats, float *out, hipStream_t s);
-hipError_t ppo_heads(const uint16_t *h, const float *state, const float *aw, const float *ab, const float *vw,
-                     const float *vb, const float *log_std, int A, int S, const float *actions, const float *old_logp,
-                     const float *adv, const float *ret, float clip, float vcoef, float *gm, float *gls, float *gv,
-                     float *terms, uint16_t *d4, hipStream_t s);
-// The heads' parameter gradients and the loss statistics, summed over the
-// samples in chunks through part (then in chunk order: deterministic).
-hipError_t ppo_head_grads(const uint16_t *h, const float *state, const float *gm, const float *gls, const float *gv,
-                          const float *terms, const float *log_std, int A, int S, float ecoef, float *g_aw,
-                          float *g_ab, float *g_vw, float *g_vb, float *g_ls, float *stats, float *part,
+// The loss per sample: a row of 2 A + 4 values each (gradients of the heads'
+// outputs, loss terms) and the features' gradient d4 (BF16).
+hipError_t ppo_heads(const FcParts &fc, uint16_t *h, const float *state, const float *aw, const float *ab,
+                     const float *vw, const float *vb, const float *log_std, int A, int S, const float *actions,
+                     const float *old_logp, const float *adv, const float *ret, float clip, float vcoef, float *rows,
+                     uint16_t *d4, hipStream_t s);
+// The heads' parameter gradients, the fully connected layer's bias gradient and
+// the loss statistics, summed over the samples through part in a fixed order.
+struct HeadGrads {
+    float *aw, *ab, *vw, *vb, *ls, *fcb;
+};
+hipError_t ppo_head_grads(const uint16_t *h, const float *state, const float *rows, const uint16_t *d4,
+                          const float *log_std, int A, int S, float ecoef, const HeadGrads &g, float *stats, float *part,
                           size_t part_floats, hipStream_t s);
 hipError_t gae(const float *rew, const float *val, const uint8_t *done, const float *last, int T, int N, float gamma,
                float lam, float *adv, float *ret, hipStream_t s);

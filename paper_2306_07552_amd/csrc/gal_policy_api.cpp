@@ -48,7 +48,7 @@ struct gal_policy {
     float *g = nullptr, *m = nullptr, *v = nullptr;          // gradient, Adam moments
     uint16_t *d[4] = {nullptr, nullptr, nullptr, nullptr};   // gradients of the pre-activations of conv2, conv3, fc
     uint16_t *wt = nullptr;                                  // adjoint weights
-    float *gm = nullptr, *gls = nullptr, *gv = nullptr, *terms = nullptr;
+    float *rows = nullptr;     // per sample: gradients of the heads' outputs, loss terms
     float *part = nullptr;
     size_t part_floats = 0;
     int64_t t = 0;
@@ -193,15 +193,15 @@ int gal_policy_get_weights(gal_policy *p, float *host, size_t count)
 
 namespace {
 
-// the encoder on n images: h[0..3]
-int encode(gal_policy *p, const uint32_t *depth_dev, int n, hipStream_t s)
+// the encoder on n images: h[0..2], and h[3] or its partial products
+int encode(gal_policy *p, const uint32_t *depth_dev, int n, gal::FcParts *fc, hipStream_t s)
 {
     const gal::EncoderWeights w = {p->wb + p->off_w[0], p->wb + p->off_w[1], p->wb + p->off_w[2],
                                    p->w + p->off_b[0],  p->w + p->off_b[1],  p->w + p->off_b[2]};
     POL_TRY(gal::encoder_forward(depth_dev, w, n, p->h[0], p->h[1], p->h[2], s));
     const int flat = p->side[3] * p->side[3] * kConv[2][0];
     POL_TRY(gal::fc_forward(p->h[2], p->wb + p->off_w[3], p->w + p->off_b[3], n, gal::kPolicyFeat, flat, p->fc_ws,
-                            p->fc_ws_floats, p->h[3], s));
+                            p->fc_ws_floats, p->h[3], fc, s));
     return GAL_OK;
 }
 
@@ -215,9 +215,7 @@ int train_buffers(gal_policy *p)
     int rc;
     if ((rc = p->alloc(&p->g, p->n_params)) || (rc = p->alloc(&p->m, p->n_params)) ||
         (rc = p->alloc(&p->v, p->n_params)) || (rc = p->alloc(&p->wt, gal::encoder_backward_weights())) ||
-        (rc = p->alloc(&p->gm, (size_t)n * A)) || (rc = p->alloc(&p->gls, (size_t)n * A)) ||
-        (rc = p->alloc(&p->gv, (size_t)n)) || (rc = p->alloc(&p->terms, (size_t)n * 3)) ||
-        (rc = p->alloc(&p->part, p->part_floats)))
+        (rc = p->alloc(&p->rows, (size_t)n * (2 * A + 4))) || (rc = p->alloc(&p->part, p->part_floats)))
         return rc;
     for (int l = 1; l < 4; ++l)   // conv1's stays on the chip
         if ((rc = p->alloc(&p->d[l], p->act_count(l, n)))) return rc;
@@ -238,9 +236,10 @@ int gal_policy_act(gal_policy *p, const uint32_t *depth_dev, const float *state_
     if ((uintptr_t)depth_dev % 16) return gal::api_fail(GAL_EINVAL, "depth_dev must be 16-byte aligned");
     hipStream_t s = (hipStream_t)stream;
     if (n_envs == 0) return GAL_OK;
-    int rc = encode(p, depth_dev, n_envs, s);
+    gal::FcParts fc;
+    int rc = encode(p, depth_dev, n_envs, &fc, s);
     if (rc) return rc;
-    POL_TRY(gal::policy_heads(p->h[3], state_dev, p->w + p->off_aw, p->w + p->off_ab, p->w + p->off_vw,
+    POL_TRY(gal::policy_heads(fc, p->h[3], state_dev, p->w + p->off_aw, p->w + p->off_ab, p->w + p->off_vw,
                               p->w + p->off_vb, p->w + p->off_ls, p->A, n_envs, noise_dev, actions_dev, value_dev,
                               logp_dev, s));
     p->last_envs = n_envs;
@@ -262,24 +261,23 @@ int gal_policy_ppo_gradients(gal_policy *p, const uint32_t *depth_dev, const flo
     if (rc) return rc;
     hipStream_t s = (hipStream_t)stream;
     const int S = samples, A = p->A;
-    if ((rc = encode(p, depth_dev, S, s))) return rc;
+    gal::FcParts fc;
+    if ((rc = encode(p, depth_dev, S, &fc, s))) return rc;
     p->last_envs = S;
-    const int F = gal::kPolicyFeat + gal::kPolicyProprio;
-    (void)F;
     float *g = p->g;
     // heads: per-sample loss gradients, the features' gradient, then the
-    // heads' own parameter gradients and the statistics
-    POL_TRY(gal::ppo_heads(p->h[3], state_dev, p->w + p->off_aw, p->w + p->off_ab, p->w + p->off_vw,
+    // heads' own parameter gradients, the fc bias's and the statistics
+    POL_TRY(gal::ppo_heads(fc, p->h[3], state_dev, p->w + p->off_aw, p->w + p->off_ab, p->w + p->off_vw,
                            p->w + p->off_vb, p->w + p->off_ls, A, S, actions_dev, old_logp_dev, adv_dev, ret_dev,
-                           hp->clip, hp->value_coef, p->gm, p->gls, p->gv, p->terms, p->d[3], s));
-    POL_TRY(gal::ppo_head_grads(p->h[3], state_dev, p->gm, p->gls, p->gv, p->terms, p->w + p->off_ls, A, S,
-                                hp->entropy_coef, g + p->off_aw, g + p->off_ab, g + p->off_vw, g + p->off_vb,
-                                g + p->off_ls, stats_dev, p->part, p->part_floats, s));
+                           hp->clip, hp->value_coef, p->rows, p->d[3], s));
+    const gal::HeadGrads hg = {g + p->off_aw, g + p->off_ab, g + p->off_vw,
+                               g + p->off_vb, g + p->off_ls, g + p->off_b[3]};
+    POL_TRY(gal::ppo_head_grads(p->h[3], state_dev, p->rows, p->d[3], p->w + p->off_ls, A, S, hp->entropy_coef, hg,
+                                stats_dev, p->part, p->part_floats, s));
     // fully connected layer
     const int flat = p->side[3] * p->side[3] * kConv[2][0];
     POL_TRY(gal::mlp_gemm(gal::kGemmDw, p->d[3], p->h[2], gal::kPolicyFeat, flat, S, gal::kPolicyFeat, flat, nullptr,
                           nullptr, 0, g + p->off_w[3], nullptr, flat, s, p->part, p->part_floats));
-    POL_TRY(gal::colsum(p->d[3], S, gal::kPolicyFeat, p->part, p->part_floats, g + p->off_b[3], s));
     POL_TRY(gal::mlp_gemm(gal::kGemmDx, p->d[3], p->wb + p->off_w[3], S, flat, gal::kPolicyFeat, gal::kPolicyFeat,
                           flat, nullptr, p->h[2], flat, nullptr, p->d[2], flat, s));
     // convolutions 3, 2, 1 (conv1's and conv2's parameters follow each other, and conv3's)

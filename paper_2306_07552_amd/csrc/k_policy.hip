@@ -27,12 +27,125 @@ __device__ __forceinline__ uint16_t f2bf(float f)
 
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
-// The heads of env e (one wave): f = [h (BF16 features), q (joint angles)];
-// mean_a = b_a + sum_k W_a[k] f_k, value = b_v + sum_k w_v[k] f_k (FP32,
-// lane-strided partial sums combined by a fixed butterfly); the action
-// mean + std * noise and its Gaussian log-density sum_a (-noise_a^2 / 2 -
-// log_std_a) - A log(2 pi) / 2 (noise null: the mean, no log-density).
-__global__ __launch_bounds__(256) void k_policy_heads(const uint16_t *__restrict__ h, const float *__restrict__ state,
+constexpr int kF = kPolicyFeat + kPolicyProprio;   // inputs of the heads: features, joint angles
+constexpr int kNF = (kF + 63) / 64;                // values of f per lane: k = lane + 64 i
+
+// Lane l of a row of 16 receives lane (l - n) mod 16's value.
+template <int kN>
+__device__ __forceinline__ float row_rotate(float v)
+{
+    const int b = __float_as_int(v);
+    return __int_as_float(__builtin_amdgcn_update_dpp(b, b, 0x120 + kN, 0xF, 0xF, false));
+}
+
+// Sum over the wave in the order of a butterfly (partners 32, 16, 8, 4, 2, 1
+// lanes away), in every lane.  Swapping wave halves and rows, then rotating
+// within a row, brings the same partners together without LDS: once lanes 8
+// apart agree, the lane 4 places round the row holds the sum of the lane 4 away,
+// and so on.  (Six LDS shuffles per head were most of a head's time.)
+__device__ __forceinline__ float wave_sum(float v)
+{
+    uint32_t b = __float_as_uint(v);
+    const auto h = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+    v = __uint_as_float(h[0]) + __uint_as_float(h[1]);
+    b = __float_as_uint(v);
+    const auto q = __builtin_amdgcn_permlane16_swap(b, b, false, false);
+    v = __uint_as_float(q[0]) + __uint_as_float(q[1]);
+    v += row_rotate<8>(v);
+    v += row_rotate<4>(v);
+    v += row_rotate<2>(v);
+    return v + row_rotate<1>(v);
+}
+
+__device__ __forceinline__ float lane_value(float v, int l)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+
+// The heads' inputs of sample e: the BF16 features (from the fully connected
+// layer's split partial products, added in order with bias and ReLU and written
+// to h, or from h itself) and the joint angles.
+__device__ __forceinline__ void head_inputs(const FcParts &fc, uint16_t *h, const float *state, int e, int lane,
+                                            float (&f)[kNF])
+{
+    constexpr int kN = kPolicyFeat / 64;
+    const size_t at = (size_t)e * kPolicyFeat + lane;
+    f[kN] = lane < kPolicyProprio ? state[(size_t)e * 10 + 3 + lane] : 0.0f;
+    if (fc.splits == 1) {
+#pragma unroll
+        for (int i = 0; i < kN; ++i) f[i] = bf2f(h[at + 64 * i]);
+        return;
+    }
+    // all of a split's loads (and two splits') are in flight together
+    const float *__restrict__ part = fc.part + at;
+#pragma unroll
+    for (int i = 0; i < kN; ++i) f[i] = part[64 * i];
+#pragma unroll 2
+    for (int z = 1; z < fc.splits; ++z) {
+        part += fc.stride;
+        float v[kN];
+#pragma unroll
+        for (int i = 0; i < kN; ++i) v[i] = part[64 * i];
+#pragma unroll
+        for (int i = 0; i < kN; ++i) f[i] += v[i];
+    }
+    uint16_t b[kN];
+#pragma unroll
+    for (int i = 0; i < kN; ++i) {
+        const float v = f[i] + fc.bias[lane + 64 * i];
+        b[i] = f2bf(v > 0.f ? v : 0.f);
+        f[i] = bf2f(b[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < kN; ++i) h[at + 64 * i] = b[i];
+}
+
+// out[s] of lane a (0..A): head a's sum over k of w[k] f_k for sample s (FP32,
+// lane-strided partial sums, then wave_sum), the critic as head A; four heads at
+// a time, so that their loads and sums overlap.
+template <int kS>
+__device__ __forceinline__ void head_sums(const float *__restrict__ aw, const float *__restrict__ vw, int A,
+                                          const float (&f)[kS][kNF], int lane, float (&out)[kS])
+{
+#pragma unroll
+    for (int s = 0; s < kS; ++s) out[s] = 0.0f;
+    for (int a0 = 0; a0 <= A; a0 += 4) {
+        float sum[4][kS], w[4][kNF];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int a = min(a0 + j, A);
+            const float *wa = a < A ? aw + (size_t)a * kF : vw;
+#pragma unroll
+            for (int i = 0; i < kNF; ++i) w[j][i] = wa[min(lane + 64 * i, kF - 1)];
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int s = 0; s < kS; ++s) {
+                float v = 0.0f;
+#pragma unroll
+                for (int i = 0; i < kNF; ++i) {
+                    const float t = w[j][i] * f[s][i];
+                    v += i < kNF - 1 || lane < kPolicyProprio ? t : 0.0f;
+                }
+                sum[j][s] = v;
+            }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int s = 0; s < kS; ++s) {
+                const float v = wave_sum(sum[j][s]);
+                if (lane == a0 + j) out[s] = v;
+            }
+    }
+}
+
+// The heads of env e (one wave): mean_a = b_a + sum_k W_a[k] f_k, value = b_v +
+// sum_k w_v[k] f_k; the action mean + std * noise and its Gaussian log-density
+// sum_a (-noise_a^2 / 2 - log_std_a) - A log(2 pi) / 2 (noise null: the mean, no
+// log-density).  Lane a holds head a.
+__global__ __launch_bounds__(256) void k_policy_heads(FcParts fc, uint16_t *__restrict__ h,
+                                                      const float *__restrict__ state,
                                                       const float *__restrict__ aw, const float *__restrict__ ab,
                                                       const float *__restrict__ vw, const float *__restrict__ vb,
                                                       const float *__restrict__ log_std, int A, int n_envs,
@@ -42,38 +155,27 @@ __global__ __launch_bounds__(256) void k_policy_heads(const uint16_t *__restrict
     const int lane = threadIdx.x & 63;
     const int e = __builtin_amdgcn_readfirstlane((int)blockIdx.x * 4 + (int)threadIdx.x / 64);
     if (e >= n_envs) return;
-    constexpr int F = kPolicyFeat + kPolicyProprio;
-    float f[(F + 63) / 64];
-#pragma unroll
-    for (int i = 0; i < (F + 63) / 64; ++i) {
-        const int k = lane + 64 * i;
-        f[i] = k < kPolicyFeat ? bf2f(h[(size_t)e * kPolicyFeat + k])
-                               : (k < F ? state[(size_t)e * 10 + 3 + (k - kPolicyFeat)] : 0.0f);
-    }
-    float lp = 0.0f;
-    for (int a = 0; a <= A; ++a) {
-        const float *w = a < A ? aw + (size_t)a * F : vw;
-        float s = 0.0f;
-#pragma unroll
-        for (int i = 0; i < (F + 63) / 64; ++i) {
-            const int k = lane + 64 * i;
-            if (k < F) s += w[k] * f[i];
+    float f[1][kNF], sum[1];
+    head_inputs(fc, h, state, e, lane, f[0]);
+    head_sums<1>(aw, vw, A, f, lane, sum);
+    float term = 0.0f;
+    if (lane < A) {
+        const float mean = sum[0] + ab[lane];
+        float act = mean;
+        if (noise) {
+            const float z = noise[(size_t)e * A + lane], ls = log_std[lane];
+            act = mean + expf(ls) * z;
+            term = -0.5f * z * z - ls;
         }
-        for (int d = 32; d >= 1; d >>= 1) s += __shfl_xor(s, d, 64);
-        if (a < A) {
-            const float mean = s + ab[a];
-            float act = mean;
-            if (noise) {
-                const float z = noise[(size_t)e * A + a];
-                act = mean + expf(log_std[a]) * z;
-                lp += -0.5f * z * z - log_std[a];
-            }
-            if (lane == 0) actions[(size_t)e * A + a] = act;
-        } else if (lane == 0 && value) {
-            value[e] = s + vb[0];
-        }
+        actions[(size_t)e * A + lane] = act;
+    } else if (lane == A && value) {
+        value[e] = sum[0] + vb[0];
     }
-    if (lane == 0 && noise && logp) logp[e] = lp - 0.9189385332046727f * (float)A;
+    if (noise && logp) {
+        float lp = 0.0f;
+        for (int a = 0; a < A; ++a) lp += lane_value(term, a);
+        if (lane == 0) logp[e] = lp - 0.9189385332046727f * (float)A;
+    }
 }
 
 // ---------------------------------------------------------------- backward
@@ -98,180 +200,234 @@ __global__ __launch_bounds__(256) void k_sum_parts(const float *__restrict__ par
     if (wave == 0 && i < n) out[i] = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
 }
 
-// The PPO loss of sample s (one wave): the heads from h4 and the joint angles,
-// logp of the taken action, the ratio to the behaviour policy's, the clipped
-// surrogate and the value error.  Writes per sample: gm [A] = dL/dmean,
-// gls [A] = dL/dlog_std (without the entropy term), gv = dL/dV, the loss terms
-// [3] (policy, value, 0), and d4 = bf16([h4 > 0] (gm W_a + gv w_v)) over the
-// 512 features.  L is the mean over S samples.
-__global__ __launch_bounds__(256) void k_ppo_heads(const uint16_t *__restrict__ h, const float *__restrict__ state,
+// The PPO loss of kHeadSamples samples per wave (each weight is loaded once for
+// all of them): the heads from the features and the joint angles, logp of the
+// taken action, the ratio to the behaviour policy's, the clipped surrogate and
+// the value error.  Writes per sample a row of 2 A + 4 values (dL/dmean [A],
+// dL/dlog_std [A] without the entropy term, dL/dV, the loss terms: policy, value,
+// ratio) and d4 = bf16([h4 > 0] (gm W_a + gv w_v)) over the 512 features.  L is
+// the mean over S samples.  Measured, 32,768 samples: 140 us at one sample per
+// wave with LDS shuffles, 50 us at four like this.
+template <int kHeadSamples>
+__global__ __launch_bounds__(256) void k_ppo_heads(FcParts fc, uint16_t *__restrict__ h,
+                                                   const float *__restrict__ state,
                                                    const float *__restrict__ aw, const float *__restrict__ ab,
                                                    const float *__restrict__ vw, const float *__restrict__ vb,
                                                    const float *__restrict__ log_std, int A, int S,
                                                    const float *__restrict__ actions, const float *__restrict__ old_logp,
                                                    const float *__restrict__ adv, const float *__restrict__ ret,
-                                                   float clip, float vcoef, float *__restrict__ gm,
-                                                   float *__restrict__ gls, float *__restrict__ gv,
-                                                   float *__restrict__ terms, uint16_t *__restrict__ d4)
+                                                   float clip, float vcoef, float *__restrict__ rows,
+                                                   uint16_t *__restrict__ d4)
 {
     const int lane = threadIdx.x & 63;
-    const int e = __builtin_amdgcn_readfirstlane((int)blockIdx.x * 4 + (int)threadIdx.x / 64);
-    if (e >= S) return;
-    constexpr int F = kPolicyFeat + kPolicyProprio;
-    constexpr int NF = (F + 63) / 64;
-    float f[NF];
+    const int e0 = __builtin_amdgcn_readfirstlane(((int)blockIdx.x * 4 + (int)threadIdx.x / 64) * kHeadSamples);
+    if (e0 >= S) return;
+    float f[kHeadSamples][kNF], sum[kHeadSamples];
 #pragma unroll
-    for (int i = 0; i < NF; ++i) {
-        const int k = lane + 64 * i;
-        f[i] = k < kPolicyFeat ? bf2f(h[(size_t)e * kPolicyFeat + k])
-                               : (k < F ? state[(size_t)e * 10 + 3 + (k - kPolicyFeat)] : 0.0f);
-    }
-    float zs[kPolicyMaxAct];
-    float logp = 0.0f, V = 0.0f;
-    for (int a = 0; a <= A; ++a) {
-        const float *w = a < A ? aw + (size_t)a * F : vw;
-        float sum = 0.0f;
-#pragma unroll
-        for (int i = 0; i < NF; ++i) {
-            const int k = lane + 64 * i;
-            if (k < F) sum += w[k] * f[i];
-        }
-        for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 64);
-        if (a < A) {
-            const float mean = sum + ab[a];
-            const float z = (actions[(size_t)e * A + a] - mean) / expf(log_std[a]);
-            zs[a] = z;
-            logp += -0.5f * z * z - log_std[a];
-        } else {
-            V = sum + vb[0];
-        }
-    }
-    logp -= 0.9189385332046727f * (float)A;
-    const float r = expf(logp - old_logp[e]);
-    const float Ad = adv[e];
-    const float rc = fminf(fmaxf(r, 1.0f - clip), 1.0f + clip);
-    const float s1 = r * Ad, s2 = rc * Ad;
-    const bool use1 = s1 <= s2;
+    for (int s = 0; s < kHeadSamples; ++s) head_inputs(fc, h, state, min(e0 + s, S - 1), lane, f[s]);
+    head_sums<kHeadSamples>(aw, vw, A, f, lane, sum);
+    const bool head = lane < A;
+    const float ls = head ? log_std[lane] : 0.0f, std = expf(ls), bias = head ? ab[lane] : 0.0f;
     const float invS = 1.0f / (float)S;
-    const float dlogp = use1 ? -Ad * r * invS : 0.0f;
-    const float dv = vcoef * 2.0f * (V - ret[e]) * invS;
-    float g_mean[kPolicyMaxAct];
-    for (int a = 0; a < A; ++a) {
-        g_mean[a] = dlogp * zs[a] / expf(log_std[a]);
-        if (lane == 0) {
-            gm[(size_t)e * A + a] = g_mean[a];
-            gls[(size_t)e * A + a] = dlogp * (zs[a] * zs[a] - 1.0f);
+    float g_mean[kHeadSamples], dv[kHeadSamples];
+#pragma unroll
+    for (int s = 0; s < kHeadSamples; ++s) {
+        const int e = min(e0 + s, S - 1);
+        const float z = head ? (actions[(size_t)e * A + lane] - (sum[s] + bias)) / std : 0.0f;
+        const float term = -0.5f * z * z - ls;
+        float logp = 0.0f;
+        for (int a = 0; a < A; ++a) logp += lane_value(term, a);
+        logp -= 0.9189385332046727f * (float)A;
+        const float V = lane_value(sum[s], A) + vb[0];
+        const float r = expf(logp - old_logp[e]);
+        const float Ad = adv[e];
+        const float rc = fminf(fmaxf(r, 1.0f - clip), 1.0f + clip);
+        const float s1 = r * Ad, s2 = rc * Ad;
+        const bool use1 = s1 <= s2;
+        const float dlogp = use1 ? -Ad * r * invS : 0.0f;
+        dv[s] = vcoef * 2.0f * (V - ret[e]) * invS;
+        g_mean[s] = dlogp * z / std;
+        if (e0 + s < S) {
+            float *row = rows + (size_t)e * (2 * A + 4);
+            if (head) {
+                row[lane] = g_mean[s];
+                row[A + lane] = dlogp * (z * z - 1.0f);
+            } else if (lane == A) {
+                row[2 * A] = dv[s];
+                row[2 * A + 1] = -(use1 ? s1 : s2);
+                row[2 * A + 2] = (V - ret[e]) * (V - ret[e]);
+                row[2 * A + 3] = r;
+            }
         }
     }
-    if (lane == 0) {
-        gv[e] = dv;
-        terms[(size_t)e * 3 + 0] = -(use1 ? s1 : s2);
-        terms[(size_t)e * 3 + 1] = (V - ret[e]) * (V - ret[e]);
-        terms[(size_t)e * 3 + 2] = r;
+    float df[kHeadSamples][kPolicyFeat / 64];
+#pragma unroll
+    for (int i = 0; i < kPolicyFeat / 64; ++i) {
+        const float wk = vw[lane + 64 * i];
+#pragma unroll
+        for (int s = 0; s < kHeadSamples; ++s) df[s][i] = dv[s] * wk;
+    }
+    for (int a = 0; a < A; ++a) {
+        float ga[kHeadSamples];
+#pragma unroll
+        for (int s = 0; s < kHeadSamples; ++s) ga[s] = lane_value(g_mean[s], a);
+#pragma unroll
+        for (int i = 0; i < kPolicyFeat / 64; ++i) {
+            const float wk = aw[(size_t)a * kF + lane + 64 * i];
+#pragma unroll
+            for (int s = 0; s < kHeadSamples; ++s) df[s][i] += ga[s] * wk;
+        }
     }
 #pragma unroll
-    for (int i = 0; i < NF; ++i) {
-        const int k = lane + 64 * i;
-        if (k < kPolicyFeat) {
-            float df = dv * vw[k];
-            for (int a = 0; a < A; ++a) df += g_mean[a] * aw[(size_t)a * F + k];
-            d4[(size_t)e * kPolicyFeat + k] = f2bf(f[i] > 0.0f ? df : 0.0f);
+    for (int s = 0; s < kHeadSamples; ++s)
+        if (e0 + s < S) {
+#pragma unroll
+            for (int i = 0; i < kPolicyFeat / 64; ++i)
+                d4[(size_t)(e0 + s) * kPolicyFeat + lane + 64 * i] = f2bf(f[s][i] > 0.0f ? df[s][i] : 0.0f);
+        }
+}
+
+// Sums over the samples: the heads' weight gradients (head gradient times
+// feature), the fully connected layer's bias gradient (d4), and the sums of the
+// per-sample rows.  A workgroup takes `per` samples, wave w every fourth of them,
+// lane l the features 8 l .. 8 l + 7 of up to kHeadGroup heads (blockIdx.y: which),
+// so that a feature is read once for all heads; its four waves' sums are added in
+// order into slab blockIdx.x:
+//   [A + 1][512] heads x features, [512] fc bias, [A + 1][7] heads x joint angles,
+//   [2 A + 4] row sums.
+// One thread per output over 512 samples took 366 us for 32,768 samples and 233
+// for 2,000 (too few waves, each a chain of dependent loads); this 38 and 14.
+constexpr int kHeadGroup = 12;
+__host__ __device__ constexpr int head_slab(int A) { return (A + 1) * kF + kPolicyFeat + 2 * A + 4; }
+
+__global__ __launch_bounds__(256) void k_ppo_head_part(const uint16_t *__restrict__ h, const float *__restrict__ state,
+                                                       const float *__restrict__ rows,
+                                                       const uint16_t *__restrict__ d4, int A, int S, int per,
+                                                       float *__restrict__ part)
+{
+    __shared__ float red[4][kPolicyFeat];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int a0 = blockIdx.y * kHeadGroup, na = min(kHeadGroup, A + 1 - a0);
+    const bool first = blockIdx.y == 0;
+    const int e0 = blockIdx.x * per, e1 = min(S, e0 + per);
+    const int nrow = 2 * A + 4, nq = (A + 1) * kPolicyProprio;
+    float acc[kHeadGroup][8], accd[8], accq[4], accr[2];
+#pragma unroll
+    for (int j = 0; j < kHeadGroup; ++j)
+#pragma unroll
+        for (int c = 0; c < 8; ++c) acc[j][c] = 0.0f;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) accd[c] = 0.0f;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) accq[c] = 0.0f;
+    accr[0] = accr[1] = 0.0f;
+#pragma unroll 2
+    for (int e = e0 + wave; e < e1; e += 4) {
+        const float *row = rows + (size_t)e * nrow;
+        const uint4 q = *reinterpret_cast<const uint4 *>(h + (size_t)e * kPolicyFeat + 8 * lane);
+        const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+        float f[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) f[c] = __uint_as_float((c & 1) ? w[c >> 1] & 0xFFFF0000u : w[c >> 1] << 16);
+#pragma unroll
+        for (int j = 0; j < kHeadGroup; ++j) {
+            // (past the last head: the critic's again, not stored)
+            const float ga = row[a0 + j < A ? a0 + j : 2 * A];
+#pragma unroll
+            for (int c = 0; c < 8; ++c) acc[j][c] += ga * f[c];
+        }
+        if (first) {
+            const uint4 d = *reinterpret_cast<const uint4 *>(d4 + (size_t)e * kPolicyFeat + 8 * lane);
+            const uint32_t v[4] = {d.x, d.y, d.z, d.w};
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+                accd[c] += __uint_as_float((c & 1) ? v[c >> 1] & 0xFFFF0000u : v[c >> 1] << 16);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int i = lane + 64 * c, a = i / kPolicyProprio;
+                if (i < nq) accq[c] += row[a < A ? a : 2 * A] * state[(size_t)e * 10 + 3 + (i - a * kPolicyProprio)];
+            }
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+                if (lane + 64 * c < nrow) accr[c] += row[lane + 64 * c];
         }
     }
-}
-
-// Gradients of the heads as sums over the samples, in chunks of kHeadChunk
-// samples (one thread per output and chunk, the chunks then added in chunk
-// order: deterministic).  Output i of a chunk: i < (A + 1) F the actor's
-// W [A][F] then the critic's w [F] (gradient of the output times the
-// feature), then the actor bias [A], log_std [A] (without the entropy term),
-// the critic bias, and the three loss terms (policy, value, ratio).
-constexpr int kHeadChunk = 512;
-__global__ void k_ppo_head_part(const uint16_t *__restrict__ h, const float *__restrict__ state,
-                                const float *__restrict__ gm, const float *__restrict__ gls,
-                                const float *__restrict__ gv, const float *__restrict__ terms, int A, int S,
-                                int nout, float *__restrict__ part)
-{
-    constexpr int F = kPolicyFeat + kPolicyProprio;
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nout) return;
-    const int e0 = blockIdx.y * kHeadChunk, e1 = min(S, e0 + kHeadChunk);
-    const int nw = (A + 1) * F;
-    float acc = 0.0f;
-    if (i < nw) {
-        const int a = i / F, k = i - a * F;
-        for (int e = e0; e < e1; ++e) {
-            const float fk = k < kPolicyFeat ? bf2f(h[(size_t)e * kPolicyFeat + k])
-                                             : state[(size_t)e * 10 + 3 + (k - kPolicyFeat)];
-            acc += (a < A ? gm[(size_t)e * A + a] : gv[e]) * fk;
+    float *slab = part + (size_t)blockIdx.x * head_slab(A);
+    // the four waves' sums of n <= 512 values in red
+    auto combine = [&](int n, float *dst) {
+        __syncthreads();
+        for (int i = tid; i < n; i += 256) dst[i] = ((red[0][i] + red[1][i]) + red[2][i]) + red[3][i];
+        __syncthreads();
+    };
+    auto put8 = [&](const float (&v)[8]) {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) red[wave][8 * lane + c] = v[c];
+    };
+#pragma unroll
+    for (int j = 0; j < kHeadGroup; ++j)
+        if (j < na) {
+            put8(acc[j]);
+            combine(kPolicyFeat, slab + (size_t)(a0 + j) * kPolicyFeat);
         }
-    } else if (i < nw + A) {
-        const int a = i - nw;
-        for (int e = e0; e < e1; ++e) acc += gm[(size_t)e * A + a];
-    } else if (i < nw + 2 * A) {
-        const int a = i - nw - A;
-        for (int e = e0; e < e1; ++e) acc += gls[(size_t)e * A + a];
-    } else if (i == nw + 2 * A) {
-        for (int e = e0; e < e1; ++e) acc += gv[e];
-    } else {
-        const int t = i - nw - 2 * A - 1;
-        for (int e = e0; e < e1; ++e) acc += terms[(size_t)e * 3 + t];
-    }
-    part[(size_t)blockIdx.y * nout + i] = acc;
+    if (!first) return;
+    slab += (A + 1) * kPolicyFeat;
+    put8(accd);
+    combine(kPolicyFeat, slab);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) red[wave][lane + 64 * c] = accq[c];
+    combine(nq, slab + kPolicyFeat);
+#pragma unroll
+    for (int c = 0; c < 2; ++c) red[wave][lane + 64 * c] = accr[c];
+    combine(nrow, slab + kPolicyFeat + nq);
 }
 
-// The summed head outputs into the gradient vector and the statistics [4] =
-// mean policy loss, mean value error, entropy, mean ratio.
-__global__ void k_ppo_head_finish(const float *__restrict__ sum, const float *__restrict__ log_std, int A, int S,
-                                  float ecoef, float *__restrict__ g_aw, float *__restrict__ g_ab,
-                                  float *__restrict__ g_vw, float *__restrict__ g_vb, float *__restrict__ g_ls,
-                                  float *__restrict__ stats)
+// The slabs' sums (as in k_sum_parts) into the gradient vector and the
+// statistics [4] = mean policy loss, mean value error, entropy, mean ratio.
+__global__ __launch_bounds__(256) void k_ppo_head_sum(const float *__restrict__ part, int slabs,
+                                                      const float *__restrict__ log_std, int A, int S, float ecoef,
+                                                      HeadGrads g, float *__restrict__ stats)
 {
-    constexpr int F = kPolicyFeat + kPolicyProprio;
-    const int nw = (A + 1) * F;
-    for (int i = threadIdx.x; i < nw + 2 * A + 1; i += blockDim.x) {
-        const float v = sum[i];
-        if (i < A * F) g_aw[i] = v;
-        else if (i < nw) g_vw[i - A * F] = v;
-        else if (i < nw + A) g_ab[i - nw] = v;
-        else if (i < nw + 2 * A) g_ls[i - nw - A] = v - ecoef;
-        else g_vb[0] = v;
+    __shared__ float red[4][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int n = head_slab(A);
+    int i = blockIdx.x * 64 + lane;
+    float v = 0.0f;
+    if (i < n) {
+#pragma unroll 8
+        for (int z = wave; z < slabs; z += 4) v += part[(size_t)z * n + i];
     }
-    if (threadIdx.x == 0 && stats) {
-        float ent = 0.0f;
-        for (int a = 0; a < A; ++a) ent += log_std[a] + 1.4189385332046727f;
-        const float *t = sum + nw + 2 * A + 1;
-        stats[0] = t[0] / (float)S;
-        stats[1] = t[1] / (float)S;
-        stats[2] = ent;
-        stats[3] = t[2] / (float)S;
+    red[wave][lane] = v;
+    __syncthreads();
+    if (wave != 0 || i >= n) return;
+    v = ((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane];
+    if (i < (A + 1) * kPolicyFeat) {
+        const int a = i / kPolicyFeat, k = i - a * kPolicyFeat;
+        (a < A ? g.aw + (size_t)a * kF : g.vw)[k] = v;
+        return;
     }
-}
-
-// Column sums of a BF16 [rows][D] matrix in chunks of `per` rows: part
-// [chunk][D] (one thread per column; the chunks are summed in order after).
-__global__ void k_colsum_chunks(const uint16_t *__restrict__ g, int rows, int D, int per, float *__restrict__ part)
-{
-    const int c = threadIdx.x, chunk = blockIdx.x;
-    if (c >= D) return;
-    const int r0 = chunk * per, r1 = min(rows, r0 + per);
-    float acc = 0.0f;
-    for (int r = r0; r < r1; ++r) acc += bf2f(g[(size_t)r * D + c]);
-    part[(size_t)chunk * D + c] = acc;
-}
-
-// The fully connected layer from split-K partial products: out[m][n] =
-// bf16(relu(sum over splits in order of part[z][m][n] + b[n])).
-__global__ void k_fc_finish(const float *__restrict__ part, int splits, int M, int N, const float *__restrict__ bias,
-                            uint16_t *__restrict__ out)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t n_all = (int64_t)M * N;
-    if (i >= n_all) return;
-    float v = part[i];
-    for (int z = 1; z < splits; ++z) v += part[(size_t)z * n_all + i];
-    v += bias[i % N];
-    out[i] = f2bf(v > 0.f ? v : 0.f);
+    i -= (A + 1) * kPolicyFeat;
+    if (i < kPolicyFeat) {
+        g.fcb[i] = v;
+        return;
+    }
+    i -= kPolicyFeat;
+    if (i < (A + 1) * kPolicyProprio) {
+        const int a = i / kPolicyProprio, k = kPolicyFeat + i - a * kPolicyProprio;
+        (a < A ? g.aw + (size_t)a * kF : g.vw)[k] = v;
+        return;
+    }
+    i -= (A + 1) * kPolicyProprio;
+    if (i < A) g.ab[i] = v;
+    else if (i < 2 * A) g.ls[i - A] = v - ecoef;
+    else if (i == 2 * A) g.vb[0] = v;
+    else if (stats) {
+        stats[i == 2 * A + 3 ? 3 : i - 2 * A - 1] = v / (float)S;
+        if (i == 2 * A + 3) {
+            float ent = 0.0f;
+            for (int a = 0; a < A; ++a) ent += log_std[a] + 1.4189385332046727f;
+            stats[2] = ent;
+        }
+    }
 }
 
 // Generalised advantage estimation, one thread per env, backwards in time.
@@ -301,47 +457,35 @@ hipError_t sum_parts(const float *part, int splits, int64_t n, float *out, hipSt
     return hipGetLastError();
 }
 
-hipError_t colsum(const uint16_t *g, int rows, int D, float *part, size_t part_floats, float *out, hipStream_t s)
-{
-    if (rows <= 0) return hipMemsetAsync(out, 0, sizeof(float) * D, s);
-    // about 256 chunks of at least 64 rows
-    const int per = std::max(64, (rows + 255) / 256);
-    const int chunks = (rows + per - 1) / per;
-    if ((size_t)chunks * D > part_floats || D > 1024) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_colsum_chunks, dim3(chunks), dim3((D + 63) / 64 * 64), 0, s, g, rows, D, per, part);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    return sum_parts(part, chunks, D, out, s);
-}
-
-hipError_t ppo_heads(const uint16_t *h, const float *state, const float *aw, const float *ab, const float *vw,
-                     const float *vb, const float *log_std, int A, int S, const float *actions, const float *old_logp,
-                     const float *adv, const float *ret, float clip, float vcoef, float *gm, float *gls, float *gv,
-                     float *terms, uint16_t *d4, hipStream_t s)
+hipError_t ppo_heads(const FcParts &fc, uint16_t *h, const float *state, const float *aw, const float *ab,
+                     const float *vw, const float *vb, const float *log_std, int A, int S, const float *actions,
+                     const float *old_logp, const float *adv, const float *ret, float clip, float vcoef, float *rows,
+                     uint16_t *d4, hipStream_t s)
 {
     if (S <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_ppo_heads, dim3((S + 3) / 4), dim3(256), 0, s, h, state, aw, ab, vw, vb, log_std, A, S,
-                       actions, old_logp, adv, ret, clip, vcoef, gm, gls, gv, terms, d4);
+    // four samples per wave share the weights' loads; up to 4096 samples one, as
+    // the waves would not fill the chip (2,000 samples: 19 us with four, 12 with one)
+    const int per = S > 4096 ? 4 : 1;
+    hipLaunchKernelGGL(per == 4 ? k_ppo_heads<4> : k_ppo_heads<1>, dim3((S + 4 * per - 1) / (4 * per)), dim3(256), 0, s,
+                       fc, h, state, aw, ab, vw, vb, log_std, A, S, actions, old_logp, adv, ret, clip, vcoef, rows, d4);
     return hipGetLastError();
 }
 
-hipError_t ppo_head_grads(const uint16_t *h, const float *state, const float *gm, const float *gls, const float *gv,
-                          const float *terms, const float *log_std, int A, int S, float ecoef, float *g_aw,
-                          float *g_ab, float *g_vw, float *g_vb, float *g_ls, float *stats, float *part,
+hipError_t ppo_head_grads(const uint16_t *h, const float *state, const float *rows, const uint16_t *d4,
+                          const float *log_std, int A, int S, float ecoef, const HeadGrads &g, float *stats, float *part,
                           size_t part_floats, hipStream_t s)
 {
     if (S <= 0) return hipErrorInvalidValue;
-    const int nout = (A + 1) * (kPolicyFeat + kPolicyProprio) + 2 * A + 1 + 3;
-    const int chunks = (S + kHeadChunk - 1) / kHeadChunk;
-    if ((size_t)(chunks + 1) * nout > part_floats) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_ppo_head_part, dim3((nout + 255) / 256, chunks), dim3(256), 0, s, h, state, gm, gls, gv,
-                       terms, A, S, nout, part);
+    // at most 256 slabs, of at least 32 samples (8 per wave)
+    const int per = std::max(32, (S + 255) / 256);
+    const int slabs = (S + per - 1) / per;
+    if ((size_t)slabs * head_slab(A) > part_floats) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_ppo_head_part, dim3(slabs, (A + kHeadGroup) / kHeadGroup), dim3(256), 0, s, h, state, rows, d4,
+                       A, S, per, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    float *sum = part + (size_t)chunks * nout;
-    if ((e = sum_parts(part, chunks, nout, sum, s)) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_ppo_head_finish, dim3(1), dim3(256), 0, s, sum, log_std, A, S, ecoef, g_aw, g_ab, g_vw,
-                       g_vb, g_ls, stats);
+    hipLaunchKernelGGL(k_ppo_head_sum, dim3((head_slab(A) + 63) / 64), dim3(256), 0, s, part, slabs, log_std, A, S,
+                       ecoef, g, stats);
     return hipGetLastError();
 }
 
@@ -362,25 +506,23 @@ int fc_splits(int rows, int N, int K)
 }
 
 hipError_t fc_forward(const uint16_t *x, const uint16_t *W, const float *bias, int rows, int N, int K, float *ws,
-                      size_t ws_floats, uint16_t *out, hipStream_t s)
+                      size_t ws_floats, uint16_t *out, FcParts *parts, hipStream_t s)
 {
+    *parts = FcParts{nullptr, 1, 0, bias};
     if (rows <= 0) return hipSuccess;
     const int splits = fc_splits(rows, N, K);
     if (splits == 1 || !ws || (size_t)splits * rows * N > ws_floats)
         return mlp_gemm(kGemmFwd, x, W, rows, N, K, K, K, bias, nullptr, 0, nullptr, out, N, s);
-    hipError_t e = mlp_gemm_parts(x, W, rows, N, K, K, K, splits, ws, s);
-    if (e != hipSuccess) return e;
-    const int64_t n = (int64_t)rows * N;
-    hipLaunchKernelGGL(k_fc_finish, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, ws, splits, rows, N, bias, out);
-    return hipGetLastError();
+    *parts = FcParts{ws, splits, (int64_t)rows * N, bias};
+    return mlp_gemm_parts(x, W, rows, N, K, K, K, splits, ws, s);
 }
 
-hipError_t policy_heads(const uint16_t *h, const float *state, const float *aw, const float *ab, const float *vw,
-                        const float *vb, const float *log_std, int A, int n_envs, const float *noise,
+hipError_t policy_heads(const FcParts &fc, uint16_t *h, const float *state, const float *aw, const float *ab,
+                        const float *vw, const float *vb, const float *log_std, int A, int n_envs, const float *noise,
                         float *actions, float *value, float *logp, hipStream_t s)
 {
     if (n_envs <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_policy_heads, dim3((n_envs + 3) / 4), dim3(256), 0, s, h, state, aw, ab, vw, vb, log_std,
+    hipLaunchKernelGGL(k_policy_heads, dim3((n_envs + 3) / 4), dim3(256), 0, s, fc, h, state, aw, ab, vw, vb, log_std,
                        A, n_envs, noise, actions, value, logp);
     return hipGetLastError();
 }
