@@ -11,7 +11,7 @@ CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libgal.so")
 
 SOURCES = ["gal_api.cpp", "gal_mlp_api.cpp", "k_robot.hip", "k_grid.hip", "k_raster.hip",
-           "k_util.hip", "k_mlp.hip", "k_gemm.hip", "k_surrogate.hip", "k_sur_infer.hip",
+           "k_util.hip", "k_mlp.hip", "k_gemm.hip", "k_mlp_train.hip", "k_surrogate.hip", "k_sur_infer.hip",
            "gal_noalloc.cpp", "k_policy.hip", "k_policy_enc.hip", "k_policy_bwd.hip", "gal_policy_api.cpp"]
 
 # Exact binary32 semantics on the device: no contraction into FMA, correctly

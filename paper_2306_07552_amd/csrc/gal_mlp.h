@@ -39,12 +39,44 @@ hipError_t gemm_tiles(int variant, const uint16_t *A, const uint16_t *B, int M, 
 hipError_t mlp_gemm(int variant, const uint16_t *A, const uint16_t *B, int M, int N, int K, int lda,
                     int ldb, const float *bias, const uint16_t *mask, int ldm, float *Cf,
                     uint16_t *Cb, int ldc, hipStream_t s, float *ws = nullptr, size_t ws_floats = 0);
-hipError_t mlp_head_fwd(const uint16_t *h, const uint16_t *w, const float *b, int rows, int D,
-                        float *z, hipStream_t s);
-hipError_t mlp_loss(const float *z, const float *y, int rows, float pos_w, float *dz, float *loss,
-                    hipStream_t s);
-hipError_t mlp_head_bwd(const uint16_t *h, const uint16_t *w, const float *dz, int rows, int D,
-                        uint16_t *dpre, float *dw, float *db, hipStream_t s);
+// Training, between the first layer's output h1 (BF16 [rows][256], ReLU) and the
+// weight gradients: layers 2..4, the logit, the weighted logistic loss and the
+// pre-activation gradients of layers 1..4 (dp[0..3], BF16 [rows][256]); h2, h3
+// go to memory for the weight gradients, the logit's gradients and the loss into
+// `slabs` slabs of part.  wf, wt: the layers' copies by mlp_mid_layout.
+struct MlpMidArgs {
+    const uint16_t *h1;
+    uint16_t *h2, *h3, *dp[4];
+    const uint16_t *wf, *wt;
+    const float *b[3];     // biases of layers 2..4
+    const uint16_t *w5;    // the logit's weights, bias
+    const float *b5;
+    const float *y;
+    int rows;
+    float pos_w;
+    float *part;
+};
+size_t mlp_mid_weights();       // BF16 values of wf, and of wt
+size_t mlp_mid_part_floats();
+hipError_t mlp_mid_layout(const uint16_t *w1, const uint16_t *w2, const uint16_t *w3, uint16_t *wf, uint16_t *wt,
+                          hipStream_t s);
+hipError_t mlp_mid(const MlpMidArgs &a, int *slabs, hipStream_t s);
+// Weight and bias gradients of up to four layers in one launch: job l is dY^T X
+// (dY [rows][256], X [rows][N], both 16-byte aligned) at w of each split's slab
+// (slab_floats values) and dY's column sums at b.
+struct DwJob {
+    const uint16_t *dy, *x;
+    int N;
+    int64_t w, b;
+};
+hipError_t gemm_dw_group(const DwJob *jobs, int n, int rows, float *part, int64_t slab_floats, size_t part_floats,
+                         int *splits, hipStream_t s);
+// The gradient vector from the splits' slabs (n values, from i0 on) and the
+// logit's, into g and grads (may be null); the loss into loss and loss_out (may
+// be null).
+hipError_t mlp_grad_sum(const float *part, int splits, int64_t i0, int64_t n, const float *hpart, int hslabs, float *g,
+                        float *grads, float *loss, float *loss_out, hipStream_t s);
+// Column sums of a BF16 [rows][D] matrix.
 hipError_t mlp_colsum(const uint16_t *g, int rows, int D, float *out, hipStream_t s);
 hipError_t mlp_adam(float *w, float *m, float *v, const float *g, int64_t n, float lr, float b1,
                     float b2, float eps, int64_t t, uint16_t *wb, hipStream_t s);
@@ -140,8 +172,8 @@ size_t sur_infer_layout_elems();
 hipError_t sur_infer_layout(const uint16_t *w0, const uint16_t *w1, const uint16_t *w2, const uint16_t *w3,
                             uint16_t *wi, hipStream_t s);
 
-// Rewrites m's inference copy of the weights (call after they change).
-hipError_t mlp_refresh_inference(gal_mlp *m, hipStream_t s);
+// Rewrites m's inference and training copies of the weights (call after they change).
+hipError_t mlp_refresh_copies(gal_mlp *m, hipStream_t s);
 // Inference of the MLP m (gal_mlp_api.cpp); part null = the MLP's own scratch.
 int mlp_infer_rows(gal_mlp *m, const uint16_t *x, const SurInferArgs *src, int rows, float *z,
                    const RouteArgs *route, hipStream_t s, float *part = nullptr);

@@ -38,9 +38,11 @@ struct gal_mlp {
     float *w = nullptr, *m = nullptr, *v = nullptr, *g = nullptr;
     uint16_t *wb = nullptr;
     uint16_t *wi = nullptr;     // inference copy of the matrix layers (fragment order)
-    uint16_t *h[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};   // h[1..4]
-    uint16_t *dp[2] = {nullptr, nullptr};
-    float *z = nullptr, *dz = nullptr, *loss = nullptr;
+    uint16_t *wf = nullptr, *wt = nullptr;   // training copies of layers 2..4 (forward, transposed)
+    uint16_t *h[4] = {nullptr, nullptr, nullptr, nullptr};    // h[1..3]
+    uint16_t *dp[4] = {nullptr, nullptr, nullptr, nullptr};   // pre-activation gradients of layers 1..4
+    float *z = nullptr, *loss = nullptr;
+    float *head_part = nullptr; // the logit's gradients and the loss, per workgroup
     float *part = nullptr;      // inference: the first layer's partial sums
     float *dw_part = nullptr;   // split-K partial sums of the weight gradients
     size_t dw_part_floats = 0;
@@ -91,17 +93,17 @@ int gal_mlp_create(int32_t max_rows, uint64_t seed, gal_mlp **out)
     if ((rc = m->alloc(&m->w, off)) || (rc = m->alloc(&m->m, off)) || (rc = m->alloc(&m->v, off)) ||
         (rc = m->alloc(&m->g, off)) || (rc = m->alloc(&m->wb, off)) ||
         (rc = m->alloc(&m->wi, gal::sur_infer_layout_elems())) ||
-        (rc = m->alloc(&m->dp[0], (size_t)max_rows * gal::kMlpHidden)) ||
-        (rc = m->alloc(&m->dp[1], (size_t)max_rows * gal::kMlpHidden)) ||
-        (rc = m->alloc(&m->z, max_rows)) || (rc = m->alloc(&m->dz, max_rows)) ||
+        (rc = m->alloc(&m->wf, gal::mlp_mid_weights())) || (rc = m->alloc(&m->wt, gal::mlp_mid_weights())) ||
+        (rc = m->alloc(&m->z, max_rows)) || (rc = m->alloc(&m->head_part, gal::mlp_mid_part_floats())) ||
         (rc = m->alloc(&m->part, gal::sur_infer_part_floats_max(max_rows))) ||
         (rc = m->alloc(&m->dw_part, (m->dw_part_floats = (size_t)gal::kMaxDwSplits * kDims[1] * kDims[0]))) ||
         (rc = m->alloc(&m->loss, 1))) {
         delete m;
         return rc;
     }
-    for (int l = 1; l <= 4; ++l)
-        if ((rc = m->alloc(&m->h[l], (size_t)max_rows * gal::kMlpHidden))) {
+    for (int l = 0; l < 4; ++l)
+        if ((l > 0 && (rc = m->alloc(&m->h[l], (size_t)max_rows * gal::kMlpHidden))) ||
+            (rc = m->alloc(&m->dp[l], (size_t)max_rows * gal::kMlpHidden))) {
             delete m;
             return rc;
         }
@@ -130,7 +132,7 @@ int gal_mlp_set_weights(gal_mlp *m, const float *host, size_t count)
     MLP_TRY(hipMemset(m->m, 0, sizeof(float) * count));
     MLP_TRY(hipMemset(m->v, 0, sizeof(float) * count));
     MLP_TRY(gal::mlp_to_bf16(m->w, (int64_t)count, m->wb, nullptr));
-    MLP_TRY(gal::mlp_refresh_inference(m, nullptr));
+    MLP_TRY(gal::mlp_refresh_copies(m, nullptr));
     MLP_TRY(hipDeviceSynchronize());
     m->t = 0;
     return GAL_OK;
@@ -151,25 +153,13 @@ namespace gal {
 
 int mlp_max_rows(const gal_mlp *m) { return m->max_rows; }
 
-// the inference copy of the matrix layers, after the BF16 weights changed
-hipError_t mlp_refresh_inference(gal_mlp *m, hipStream_t s)
+// the inference and training copies of the matrix layers, after the BF16 weights changed
+hipError_t mlp_refresh_copies(gal_mlp *m, hipStream_t s)
 {
+    hipError_t e = mlp_mid_layout(m->wb + m->off_w[1], m->wb + m->off_w[2], m->wb + m->off_w[3], m->wf, m->wt, s);
+    if (e != hipSuccess) return e;
     return sur_infer_layout(m->wb + m->off_w[0], m->wb + m->off_w[1], m->wb + m->off_w[2],
                             m->wb + m->off_w[3], m->wi, s);
-}
-
-// forward pass of rows inputs (BF16 [rows][2112]) into m->h[1..4] and m->z
-int mlp_forward_rows(gal_mlp *m, const uint16_t *x, int rows, hipStream_t s)
-{
-    const uint16_t *in = x;
-    for (int l = 0; l < 4; ++l) {
-        MLP_TRY(mlp_gemm(kGemmFwd, in, m->wb + m->off_w[l], rows, kDims[l + 1], kDims[l], kDims[l],
-                         kDims[l], m->w + m->off_b[l], nullptr, 0, nullptr, m->h[l + 1], kDims[l + 1],
-                         s));
-        in = m->h[l + 1];
-    }
-    MLP_TRY(mlp_head_fwd(m->h[4], m->wb + m->off_w[4], m->w + m->off_b[4], rows, kMlpHidden, m->z, s));
-    return GAL_OK;
 }
 
 // inference: the inputs x, or (x null) the features of the batch envs
@@ -196,30 +186,47 @@ int mlp_infer_rows(gal_mlp *m, const uint16_t *x, const SurInferArgs *src, int r
     return GAL_OK;
 }
 
-int mlp_gradients_rows(gal_mlp *m, const uint16_t *x, const float *y, int rows, float pos_w,
-                       hipStream_t s)
+// The loss and its gradient over rows inputs into m->loss and m->g, and into
+// loss_out and grads (may be null): the first layer, everything up to the
+// pre-activation gradients, all weight gradients, their sums.
+int mlp_gradients_rows(gal_mlp *m, const uint16_t *x, const float *y, int rows, float pos_w, float *grads,
+                       float *loss_out, hipStream_t s)
 {
-    int rc = mlp_forward_rows(m, x, rows, s);
-    if (rc) return rc;
-    MLP_TRY(hipMemsetAsync(m->loss, 0, sizeof(float), s));
-    MLP_TRY(mlp_loss(m->z, y, rows, pos_w, m->dz, m->loss, s));
-    MLP_TRY(mlp_head_bwd(m->h[4], m->wb + m->off_w[4], m->dz, rows, kMlpHidden, m->dp[0],
-                         m->g + m->off_w[4], m->g + m->off_b[4], s));
-    int cur = 0;
-    for (int l = 3; l >= 0; --l) {
-        const int din = kDims[l], dout = kDims[l + 1];
-        const uint16_t *hin = l == 0 ? x : m->h[l];
-        // dW_l [dout][din] = dpre^T h_{l-1}
-        MLP_TRY(mlp_gemm(kGemmDw, m->dp[cur], hin, dout, din, rows, dout, din, nullptr, nullptr, 0,
-                         m->g + m->off_w[l], nullptr, din, s, m->dw_part, m->dw_part_floats));
-        MLP_TRY(mlp_colsum(m->dp[cur], rows, dout, m->g + m->off_b[l], s));
-        if (l > 0) {
-            // dpre_{l-1} = bf16((dpre W_l) * [h_{l-1} > 0])
-            MLP_TRY(mlp_gemm(kGemmDx, m->dp[cur], m->wb + m->off_w[l], rows, din, dout, dout, din,
-                             nullptr, m->h[l], din, nullptr, m->dp[cur ^ 1], din, s));
-            cur ^= 1;
-        }
+    MLP_TRY(mlp_gemm(kGemmFwd, x, m->wb + m->off_w[0], rows, kMlpHidden, kMlpIn, kMlpIn, kMlpIn, m->w + m->off_b[0],
+                     nullptr, 0, nullptr, m->h[1], kMlpHidden, s));
+    MlpMidArgs a = {};
+    a.h1 = m->h[1];
+    a.h2 = m->h[2];
+    a.h3 = m->h[3];
+    for (int l = 0; l < 4; ++l) a.dp[l] = m->dp[l];
+    a.wf = m->wf;
+    a.wt = m->wt;
+    for (int l = 0; l < 3; ++l) a.b[l] = m->w + m->off_b[l + 1];
+    a.w5 = m->wb + m->off_w[4];
+    a.b5 = m->w + m->off_b[4];
+    a.y = y;
+    a.rows = rows;
+    a.pos_w = pos_w;
+    a.part = m->head_part;
+    int slabs = 0, splits = 0;
+    MLP_TRY(mlp_mid(a, &slabs, s));
+    // the weight gradients (inputs that are not 16-byte aligned by the general
+    // GEMM, straight into m->g)
+    const bool aligned = (uintptr_t)x % 16 == 0;
+    DwJob jobs[4];
+    int n = 0;
+    for (int l = aligned ? 0 : 1; l < 4; ++l)
+        jobs[n++] = DwJob{m->dp[l], l == 0 ? x : m->h[l], kDims[l], m->off_w[l], m->off_b[l]};
+    if (!aligned) {
+        MLP_TRY(mlp_gemm(kGemmDw, m->dp[0], x, kMlpHidden, kMlpIn, rows, kMlpHidden, kMlpIn, nullptr, nullptr, 0,
+                         m->g + m->off_w[0], nullptr, kMlpIn, s, m->dw_part, m->dw_part_floats));
+        MLP_TRY(mlp_colsum(m->dp[0], rows, kMlpHidden, m->g + m->off_b[0], s));
+        if (grads)
+            MLP_TRY(hipMemcpyAsync(grads, m->g, sizeof(float) * m->off_w[1], hipMemcpyDeviceToDevice, s));
     }
+    MLP_TRY(gemm_dw_group(jobs, n, rows, m->dw_part, m->off_w[4], m->dw_part_floats, &splits, s));
+    MLP_TRY(mlp_grad_sum(m->dw_part, splits, aligned ? 0 : m->off_w[1], m->off_w[4], m->head_part, slabs, m->g, grads,
+                         m->loss, loss_out, s));
     return GAL_OK;
 }
 
@@ -241,12 +248,7 @@ int gal_mlp_gradients(gal_mlp *m, const uint16_t *x_dev, const float *labels_dev
     if (!m || !x_dev || !labels_dev || rows < 1 || rows > m->max_rows)
         return gal::api_fail(GAL_EINVAL, "bad arguments");
     hipStream_t s = (hipStream_t)stream;
-    int rc = gal::mlp_gradients_rows(m, x_dev, labels_dev, rows, pos_weight, s);
-    if (rc) return rc;
-    if (grads_dev)
-        MLP_TRY(hipMemcpyAsync(grads_dev, m->g, sizeof(float) * m->n_params, hipMemcpyDeviceToDevice, s));
-    if (loss_dev) MLP_TRY(hipMemcpyAsync(loss_dev, m->loss, sizeof(float), hipMemcpyDeviceToDevice, s));
-    return GAL_OK;
+    return gal::mlp_gradients_rows(m, x_dev, labels_dev, rows, pos_weight, grads_dev, loss_dev, s);
 }
 
 int gal_mlp_train_step(gal_mlp *m, const uint16_t *x_dev, const float *labels_dev, int32_t rows,
@@ -255,12 +257,11 @@ int gal_mlp_train_step(gal_mlp *m, const uint16_t *x_dev, const float *labels_de
     if (!m || !x_dev || !labels_dev || rows < 1 || rows > m->max_rows || !(lr > 0.0f))
         return gal::api_fail(GAL_EINVAL, "bad arguments");
     hipStream_t s = (hipStream_t)stream;
-    int rc = gal::mlp_gradients_rows(m, x_dev, labels_dev, rows, pos_weight, s);
+    int rc = gal::mlp_gradients_rows(m, x_dev, labels_dev, rows, pos_weight, nullptr, loss_dev, s);
     if (rc) return rc;
     m->t += 1;
     MLP_TRY(gal::mlp_adam(m->w, m->m, m->v, m->g, m->n_params, lr, 0.9f, 0.999f, 1e-8f, m->t, m->wb, s));
-    MLP_TRY(gal::mlp_refresh_inference(m, s));
-    if (loss_dev) MLP_TRY(hipMemcpyAsync(loss_dev, m->loss, sizeof(float), hipMemcpyDeviceToDevice, s));
+    MLP_TRY(gal::mlp_refresh_copies(m, s));
     return GAL_OK;
 }
 

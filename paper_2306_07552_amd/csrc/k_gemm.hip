@@ -138,44 +138,47 @@ __device__ __forceinline__ bf16x8 fragment(const unsigned char *t, int blk, int 
     return tr_frag(p, p + 4 * R * 2);
 }
 
-// One TM x TN tile of one split of K per workgroup (4 waves, 2 x 2 of them).
-// Tiles are dealt to the XCDs in contiguous runs, n fastest, so that the tiles
-// that share A's rows meet in one L2.
-template <int TM, int TN, int kStages, bool kSA, bool kSB, int EPI>
-__global__ __launch_bounds__(256, 2) void k_gemm_tiles(GemmArgs g)
+// The workgroup's tile id: dealt to the XCDs in contiguous runs, so that
+// neighbouring tiles, which share rows, meet in one L2.
+__device__ __forceinline__ int tile_id()
+{
+    const int total = gridDim.x, xcd = blockIdx.x & 7, run = total >> 3, extra = total & 7;
+    return xcd * run + min(xcd, extra) + (blockIdx.x >> 3);
+}
+
+// acc = the products of one TM x TN tile over k kbeg .. kend - 1 (4 waves, 2 x 2
+// of them, 16-wide blocks); with kSums also A's column sums, in every row of
+// accs (by a B operand of ones).
+template <int TM, int TN, int kStages, bool kSA, bool kSB, bool kSums>
+__device__ __forceinline__ void tile_products(const uint16_t *a, int lda, int M, int m0, const uint16_t *b, int ldb,
+                                              int N, int n0, int kbeg, int kend, unsigned char *lds, int lane, int wave,
+                                              bool sums, floatx4 (&acc)[TM / 32][TN / 32], floatx4 (&accs)[TM / 32])
 {
     using TA = Tile<TM, kSA, false>;
     using TB = Tile<TN, kSB, true>;
-    constexpr int kBM = TM / 32, kBN = TN / 32;   // 16-wide blocks per wave
+    constexpr int kBM = TM / 32, kBN = TN / 32;
     constexpr int kStageBytes = TA::kBytes + TB::kBytes;
     constexpr int kLoads = TA::kDma + TB::kDma;   // transfers per wave and stage
     constexpr int kAhead = kStages - 1;
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[kStages * kStageBytes];
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave >> 1, wn = wave & 1;
-    const int total = gridDim.x, xcd = blockIdx.x & 7, run = total >> 3, extra = total & 7;
-    int id = xcd * run + min(xcd, extra) + (blockIdx.x >> 3);
-    const int tn = id % g.tiles_n;
-    id /= g.tiles_n;
-    const int tm = id % g.tiles_m, z = id / g.tiles_m;
-    const int m0 = tm * TM, n0 = tn * TN;
-    const int kbeg = z * g.kchunk, kend = min(g.K, kbeg + g.kchunk);
     const int nst = (kend - kbeg + kStageK - 1) / kStageK;
     TA ta;
     TB tb;
-    ta.init(m0, g.M, g.lda, wave, lane);
-    tb.init(n0, g.N, g.ldb, wave, lane);
+    ta.init(m0, M, lda, wave, lane);
+    tb.init(n0, N, ldb, wave, lane);
     const uint32_t base = lds_addr(lds);
     auto fetch = [&](int s) {
         const uint32_t buf = base + (uint32_t)(s % kStages) * kStageBytes;
-        ta.fetch(g.a, g.lda, kbeg + s * kStageK, kend - 1, buf, wave);
-        tb.fetch(g.b, g.ldb, kbeg + s * kStageK, kend - 1, buf + TA::kBytes, wave);
+        ta.fetch(a, lda, kbeg + s * kStageK, kend - 1, buf, wave);
+        tb.fetch(b, ldb, kbeg + s * kStageK, kend - 1, buf + TA::kBytes, wave);
     };
-    floatx4 acc[kBM][kBN];
 #pragma unroll
-    for (int i = 0; i < kBM; ++i)
+    for (int i = 0; i < kBM; ++i) {
 #pragma unroll
         for (int j = 0; j < kBN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+        accs[i] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+    const bf16x8 one = __builtin_bit_cast(bf16x8, quad{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u});
 #pragma unroll
     for (int s = 0; s < kAhead; ++s)
         if (s < nst) fetch(s);
@@ -203,13 +206,37 @@ __global__ __launch_bounds__(256, 2) void k_gemm_tiles(GemmArgs g)
 #pragma unroll
             for (int j = 0; j < kBN; ++j) fb[j] = fragment<TN, kSB, true>(sb, wn * kBN + j, ks, lane);
 #pragma unroll
-            for (int i = 0; i < kBM; ++i)
+            for (int i = 0; i < kBM; ++i) {
 #pragma unroll
                 for (int j = 0; j < kBN; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa[i], acc[i][j], 0, 0, 0);
+                if (kSums && sums) accs[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(one, fa[i], accs[i], 0, 0, 0);
+            }
         }
         buf = buf + 1 == kStages ? 0 : buf + 1;
     }
+}
+
+template <int TM, int TN, int kStages>
+constexpr int ring_bytes() { return kStages * (TM + TN) * kStageK * 2; }
+
+// One TM x TN tile of one split of K per workgroup, n fastest.
+template <int TM, int TN, int kStages, bool kSA, bool kSB, int EPI>
+__global__ __launch_bounds__(256, 2) void k_gemm_tiles(GemmArgs g)
+{
+    constexpr int kBM = TM / 32, kBN = TN / 32;   // 16-wide blocks per wave
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[ring_bytes<TM, TN, kStages>()];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+    int id = tile_id();
+    const int tn = id % g.tiles_n;
+    id /= g.tiles_n;
+    const int tm = id % g.tiles_m, z = id / g.tiles_m;
+    const int m0 = tm * TM, n0 = tn * TN;
+    const int kbeg = z * g.kchunk, kend = min(g.K, kbeg + g.kchunk);
+    floatx4 acc[kBM][kBN], none[kBM];
+    tile_products<TM, TN, kStages, kSA, kSB, false>(g.a, g.lda, g.M, m0, g.b, g.ldb, g.N, n0, kbeg, kend, lds, lane,
+                                                    wave, false, acc, none);
     // lane: row m = 16 (block) + lane % 16, 8 consecutive n per pair of blocks
     float *cf = g.cf;
     if (EPI == kEpiF32 && g.splits > 1) cf += (size_t)z * g.M * g.ldc;
@@ -245,6 +272,55 @@ __global__ __launch_bounds__(256, 2) void k_gemm_tiles(GemmArgs g)
                 *reinterpret_cast<bf16x8 *>(g.cb + (size_t)m * g.ldc + n) = o;
             }
         }
+    }
+}
+
+// Weight gradients of several layers in one launch (256 rows of dY^T each):
+// splits of the rows x jobs x tiles, every split's results in its own slab.  One
+// launch instead of a GEMM, its sum and a bias sum per layer.
+constexpr int kMaxJobs = 4;
+struct DwGroup {
+    DwJob job[kMaxJobs];
+    int first[kMaxJobs + 1];   // tiles before job l
+    int rows, chunk;
+    int64_t slab;
+    float *part;
+};
+
+template <int T, int kStages>
+__global__ __launch_bounds__(256, 2) void k_dw_group(DwGroup g)
+{
+    constexpr int kB = T / 32, kM = kMlpHidden;
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[ring_bytes<T, T, kStages>()];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+    int id = tile_id();
+    const int total = g.first[kMaxJobs], z = id / total;
+    id -= z * total;
+    int l = 0;
+    while (id >= g.first[l + 1]) ++l;
+    id -= g.first[l];
+    const DwJob &job = g.job[l];
+    const int tm = id % (kM / T), tn = id / (kM / T);
+    const int m0 = tm * T, n0 = tn * T;
+    const int kbeg = z * g.chunk, kend = min(g.rows, kbeg + g.chunk);
+    floatx4 acc[kB][kB], accs[kB];
+    const bool sums = tn == 0 && wn == 0;
+    tile_products<T, T, kStages, true, true, true>(job.dy, kM, kM, m0, job.x, job.N, job.N, n0, kbeg, kend, lds, lane,
+                                                   wave, sums, acc, accs);
+    float *out = g.part + (size_t)z * g.slab;
+#pragma unroll
+    for (int i = 0; i < kB; ++i) {
+        const int m = m0 + 16 * (wm * kB + i) + (lane & 15);
+#pragma unroll
+        for (int j = 0; j < kB; j += 2) {
+            const int n = n0 + 16 * (wn * kB + j) + 8 * (lane >> 4);
+            if (n >= job.N) continue;
+            floatx4 *dst = reinterpret_cast<floatx4 *>(out + job.w + (size_t)m * job.N + n);
+            dst[0] = acc[i][j];
+            dst[1] = acc[i][j + 1];
+        }
+        if (sums && lane < 16) out[job.b + m] = accs[i][0];
     }
 }
 
@@ -294,6 +370,39 @@ bool gemm_tiles_fit(bool strided_a, bool strided_b, const uint16_t *A, const uin
     if ((bias && !aligned16(bias)) || (mask && (!aligned16(mask) || ldm % 8))) return false;
     if (strided_a && (M < 8 || M % 8)) return false;
     return (strided_a && strided_b) || K % 32 == 0;   // k-contiguous rows are read in whole steps
+}
+
+hipError_t gemm_dw_group(const DwJob *jobs, int n, int rows, float *part, int64_t slab_floats, size_t part_floats,
+                         int *splits, hipStream_t s)
+{
+    if (n < 1 || n > kMaxJobs || rows < 1) return hipErrorInvalidValue;
+    // 64 x 64 tiles in three splits or so (two workgroups per CU), 128 x 128 in
+    // eleven from 8192 rows on, where the larger tile's fewer LDS reads outweigh
+    // the larger slabs' sum
+    const int T = rows >= 2048 ? 128 : 64;
+    DwGroup g = {};
+    int tiles = 0;
+    for (int l = 0; l < n; ++l) {
+        if (!aligned16(jobs[l].dy) || !aligned16(jobs[l].x) || jobs[l].N % 8) return hipErrorInvalidValue;
+        g.job[l] = jobs[l];
+        g.first[l] = tiles;
+        tiles += (kMlpHidden / T) * ((jobs[l].N + T - 1) / T);
+    }
+    for (int l = n; l <= kMaxJobs; ++l) g.first[l] = tiles;
+    int sp = std::min((T == 64 ? 540 : 512) / tiles, rows / 256);
+    sp = (int)std::min<int64_t>(sp, (int64_t)(part_floats / (size_t)slab_floats));
+    sp = std::max(sp, 1);
+    if (part_floats < (size_t)slab_floats) return hipErrorInvalidValue;
+    g.rows = rows;
+    g.chunk = ((rows + sp - 1) / sp + 31) / 32 * 32;
+    g.slab = slab_floats;
+    g.part = part;
+    *splits = sp;
+    if (T == 64)
+        hipLaunchKernelGGL((k_dw_group<64, 4>), dim3(tiles * sp), dim3(256), 0, s, g);
+    else
+        hipLaunchKernelGGL((k_dw_group<128, 2>), dim3(tiles * sp), dim3(256), 0, s, g);
+    return hipGetLastError();
 }
 
 hipError_t gemm_tiles(int variant, const uint16_t *A, const uint16_t *B, int M, int N, int K, int lda, int ldb,

@@ -159,64 +159,6 @@ __global__ __launch_bounds__(256) void k_gemm(const uint16_t *__restrict__ A, co
             }
 }
 
-// logit head: z[i] = sum_j h[i][j] * w[j] + b  (one wave per row)
-__global__ void k_head_fwd(const uint16_t *__restrict__ h, const uint16_t *__restrict__ w,
-                           const float *__restrict__ b, int rows, int D, float *__restrict__ z)
-{
-    const int row = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (row >= rows) return;
-    float acc = 0.f;
-    for (int j = lane; j < D; j += 64) acc += bf2f(h[(size_t)row * D + j]) * bf2f(w[j]);
-    for (int d = 32; d >= 1; d >>= 1) acc += __shfl_xor(acc, d, 64);
-    if (lane == 0) z[row] = acc + b[0];
-}
-
-// weighted logistic loss and dz = w (sigmoid(z) - y) / rows
-__global__ void k_loss(const float *__restrict__ z, const float *__restrict__ y, int rows, float pos_w,
-                       float *__restrict__ dz, float *__restrict__ loss)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    float l = 0.f;
-    if (i < rows) {
-        const float zi = z[i], yi = y[i];
-        const float w = yi > 0.5f ? pos_w : 1.f;
-        const float p = 1.f / (1.f + expf(-zi));
-        dz[i] = w * (p - yi) / (float)rows;
-        l = w * ((zi > 0.f ? zi : 0.f) - zi * yi + log1pf(expf(-fabsf(zi)))) / (float)rows;
-    }
-    for (int d = 32; d >= 1; d >>= 1) l += __shfl_xor(l, d, 64);
-    if (loss && (threadIdx.x & 63) == 0) atomicAdd(loss, l);
-}
-
-// head backward: dpre[i][j] = bf16(dz_i * w_j * [h > 0]); dw[j] += sum_i dz_i h[i][j];
-// db += sum_i dz_i.  Block = 64 rows x D columns (thread = column); partial
-// sums are added atomically (dw, db zeroed by the caller).
-__global__ void k_head_bwd(const uint16_t *__restrict__ h, const uint16_t *__restrict__ w,
-                           const float *__restrict__ dz, int rows, int D,
-                           uint16_t *__restrict__ dpre, float *__restrict__ dw, float *__restrict__ db)
-{
-    const int j = threadIdx.x;
-    const int i0 = blockIdx.x * 64, i1 = min(rows, i0 + 64);
-    if (j < D) {
-        const float wj = bf2f(w[j]);
-        float acc = 0.f;
-        for (int i = i0; i < i1; ++i) {
-            const uint16_t hv = h[(size_t)i * D + j];
-            const float d = dz[i];
-            acc += d * bf2f(hv);
-            const bool on = (hv & 0x8000u) == 0 && (hv & 0x7FFFu) != 0;
-            dpre[(size_t)i * D + j] = f2bf(on ? d * wj : 0.f);
-        }
-        atomicAdd(&dw[j], acc);
-    }
-    if (j == 0) {
-        float acc = 0.f;
-        for (int i = i0; i < i1; ++i) acc += dz[i];
-        atomicAdd(db, acc);
-    }
-}
-
 // bias gradient: column sums of a BF16 [rows][D] matrix, 64 rows per block
 // (out zeroed by the caller)
 __global__ void k_colsum(const uint16_t *__restrict__ g, int rows, int D, float *__restrict__ out)
@@ -351,35 +293,6 @@ hipError_t mlp_gemm_parts(const uint16_t *A, const uint16_t *B, int M, int N, in
     const dim3 grid((N + kBN - 1) / kBN, (M + kBM - 1) / kBM, splits);
     hipLaunchKernelGGL((k_gemm<false, true, kEpiF32>), grid, dim3(256), 0, s, A, B, M, N, K, lda, ldb, nullptr,
                        nullptr, 0, part, nullptr, N);
-    return hipGetLastError();
-}
-
-hipError_t mlp_head_fwd(const uint16_t *h, const uint16_t *w, const float *b, int rows, int D,
-                        float *z, hipStream_t s)
-{
-    if (rows <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_head_fwd, dim3((rows + 3) / 4), dim3(256), 0, s, h, w, b, rows, D, z);
-    return hipGetLastError();
-}
-
-hipError_t mlp_loss(const float *z, const float *y, int rows, float pos_w, float *dz, float *loss,
-                    hipStream_t s)
-{
-    if (rows <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_loss, dim3((rows + 255) / 256), dim3(256), 0, s, z, y, rows, pos_w, dz, loss);
-    return hipGetLastError();
-}
-
-hipError_t mlp_head_bwd(const uint16_t *h, const uint16_t *w, const float *dz, int rows, int D,
-                        uint16_t *dpre, float *dw, float *db, hipStream_t s)
-{
-    if (D > 1024) return hipErrorInvalidValue;
-    hipError_t e = hipMemsetAsync(dw, 0, sizeof(float) * D, s);
-    if (e == hipSuccess) e = hipMemsetAsync(db, 0, sizeof(float), s);
-    if (e != hipSuccess || rows <= 0) return e;
-    const int threads = ((D + 63) / 64) * 64;
-    hipLaunchKernelGGL(k_head_bwd, dim3((rows + 63) / 64), dim3(threads), 0, s, h, w, dz, rows, D,
-                       dpre, dw, db);
     return hipGetLastError();
 }
 
