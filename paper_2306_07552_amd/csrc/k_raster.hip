@@ -103,11 +103,6 @@ __device__ __forceinline__ uint32_t depth24(float dv)
     return (uint32_t)dv;
 }
 
-struct Poly {
-    float X[8], Y[8], Z[8];
-    int n;
-};
-
 __device__ __forceinline__ bool before(float ax, float ay, float az, float bx, float by, float bz)
 {
     uint32_t a0 = __float_as_uint(ax), b0 = __float_as_uint(bx);
@@ -117,42 +112,95 @@ __device__ __forceinline__ bool before(float ax, float ay, float az, float bx, f
     return __float_as_uint(az) < __float_as_uint(bz);
 }
 
-// Sutherland-Hodgman against near, left, right, top, bottom.  A convex
-// triangle gains at most one vertex per plane (<= 8); should rounding ever
-// emit more, the extra vertices are dropped.
-__device__ __noinline__ void clip_polygon(Poly &p, float near_m)
+// Position of the k-th (from 0) set bit of the 16-bit mask w, which has more than k.
+__device__ __forceinline__ int nth_bit(uint32_t w, int k)
 {
-    for (int k = 0; k < 5 && p.n > 0; ++k) {
-        Poly q;
-        q.n = 0;
-        for (int i = 0; i < p.n; ++i) {
-            const int j = (i + p.n - 1) % p.n;   // previous vertex
-            const float cX = p.X[i], cY = p.Y[i], cZ = p.Z[i];
-            const float pX = p.X[j], pY = p.Y[j], pZ = p.Z[j];
-            const bool cin = clip_plane(cX, cY, cZ, k, near_m) >= 0.0f;
-            const bool pin = clip_plane(pX, pY, pZ, k, near_m) >= 0.0f;
-            if (cin != pin && q.n < 8) {
-                // endpoints in canonical order
-                float sX = pX, sY = pY, sZ = pZ, eX = cX, eY = cY, eZ = cZ;
-                if (before(cX, cY, cZ, pX, pY, pZ)) {
-                    sX = cX; sY = cY; sZ = cZ; eX = pX; eY = pY; eZ = pZ;
-                }
-                const float ps = clip_plane(sX, sY, sZ, k, near_m);
-                const float pe = clip_plane(eX, eY, eZ, k, near_m);
-                const float t = ps / (ps - pe);
-                q.X[q.n] = sX + t * (eX - sX);
-                q.Y[q.n] = sY + t * (eY - sY);
-                q.Z[q.n] = sZ + t * (eZ - sZ);
-                ++q.n;
-            }
-            if (cin && q.n < 8) {
-                q.X[q.n] = cX;
-                q.Y[q.n] = cY;
-                q.Z[q.n] = cZ;
-                ++q.n;
-            }
+    int pos = 0;
+#pragma unroll
+    for (int h = 8; h >= 1; h >>= 1) {
+        const int c = __popc(w & ((1u << h) - 1u));
+        if (k >= c) {
+            k -= c;
+            w >>= h;
+            pos += h;
         }
-        p = q;
+    }
+    return pos;
+}
+
+// Bits 0..7 of x spread to the even bits 0..14.
+__device__ __forceinline__ uint32_t spread8(uint32_t x)
+{
+    x = (x | (x << 4)) & 0x0F0Fu;
+    x = (x | (x << 2)) & 0x3333u;
+    return (x | (x << 1)) & 0x5555u;
+}
+
+// Sutherland-Hodgman against near, left, right, top, bottom for the wave's first
+// (up to) 8 triangles of `rest`, which are taken out of it: 8 lanes per polygon,
+// lane = vertex.  On entry X, Y, Z are the cluster's vertices (lane = vertex) and
+// `packed` its triangles' indices (lane = triangle); on return the polygon's
+// vertices, n (per polygon) how many, src the triangle's lane.  Per plane a lane
+// looks at its edge (from the previous vertex): the crossing point, if any, then
+// the vertex itself, if inside, are the edge's outputs, and output k of a polygon
+// finds its edge as the k-th set bit of the interleaved masks.  A plane that no
+// vertex of the group is behind changes nothing and is skipped.  A convex triangle
+// gains at most one vertex per plane (<= 8); should rounding ever emit more, the
+// extra vertices are dropped.
+// One lane per polygon needs it indexed dynamically, in scratch memory: about
+// 24 us of a room's image for its floor and walls, while the other waves of the
+// workgroup waited for the round's end (the step of 16 such envs 70 -> 46 us, of
+// 1024 apartments 305 -> 279).
+__device__ __forceinline__ void clip_group(uint64_t &rest, uint32_t packed, int lane, float near_m, float &X, float &Y,
+                                           float &Z, int &n, int &src)
+{
+    const int v = lane & 7, base = lane & 56;
+    uint64_t m = rest;
+    src = -1;
+    for (int k = 0; k < 8 && m; ++k) {
+        const int b = __ffsll((unsigned long long)m) - 1;
+        m &= m - 1;
+        if (lane >> 3 == k) src = b;
+    }
+    rest = m;
+    n = src >= 0 ? 3 : 0;
+    {
+        const uint32_t tri = (uint32_t)__shfl((int)packed, src >= 0 ? src : 0, 64);
+        const int vi = (int)((tri >> (8 * min(v, 2))) & 0xFFu);
+        const float x = __shfl(X, vi, 64), y = __shfl(Y, vi, 64), z = __shfl(Z, vi, 64);
+        X = x;
+        Y = y;
+        Z = z;
+    }
+#pragma unroll
+    for (int k = 0; k < 5; ++k) {
+        const bool live = v < n;
+        const bool in = live && clip_plane(X, Y, Z, k, near_m) >= 0.0f;
+        if (!__ballot(live && !in)) continue;
+        const int prev = base + (v > 0 ? v : max(n, 1)) - 1;
+        const float pX = __shfl(X, prev, 64), pY = __shfl(Y, prev, 64), pZ = __shfl(Z, prev, 64);
+        const bool pin = clip_plane(pX, pY, pZ, k, near_m) >= 0.0f;
+        const bool cross = live && in != pin;
+        // the crossing point, from the endpoints in canonical order
+        const bool swap = before(X, Y, Z, pX, pY, pZ);
+        const float sX = swap ? X : pX, sY = swap ? Y : pY, sZ = swap ? Z : pZ;
+        const float eX = swap ? pX : X, eY = swap ? pY : Y, eZ = swap ? pZ : Z;
+        const float ps = clip_plane(sX, sY, sZ, k, near_m);
+        const float pe = clip_plane(eX, eY, eZ, k, near_m);
+        const float t = ps / (ps - pe);
+        const float cX = sX + t * (eX - sX);
+        const float cY = sY + t * (eY - sY);
+        const float cZ = sZ + t * (eZ - sZ);
+        const uint32_t outs = spread8((uint32_t)(__ballot(cross) >> base) & 0xFFu) |
+                              (spread8((uint32_t)(__ballot(in) >> base) & 0xFFu) << 1);
+        n = min(__popc(outs), 8);
+        const int bit = v < n ? nth_bit(outs, v) : 0;
+        const int from = base + (bit >> 1);
+        const float x0 = __shfl(cX, from, 64), y0 = __shfl(cY, from, 64), z0 = __shfl(cZ, from, 64);
+        const float x1 = __shfl(X, from, 64), y1 = __shfl(Y, from, 64), z1 = __shfl(Z, from, 64);
+        X = (bit & 1) ? x1 : x0;
+        Y = (bit & 1) ? y1 : y0;
+        Z = (bit & 1) ? z1 : z0;
     }
 }
 
@@ -1067,48 +1115,41 @@ __device__ void draw_cluster(const Ctx &c, const ClusterData &d, int lane, const
     const uint64_t cmask = __ballot(clipped);
     stat_add(stats, kStatTrisValid, lane, __popcll(vmask));
     stat_add(stats, kStatTrisClipped, lane, __popcll(cmask));
-    const int vx0 = __shfl(xi, i0, 64), vy0 = __shfl(yi, i0, 64);
-    const int vx1 = __shfl(xi, i1, 64), vy1 = __shfl(yi, i1, 64);
-    const int vx2 = __shfl(xi, i2, 64), vy2 = __shfl(yi, i2, 64);
-    const float vd0 = __shfl(dv, i0, 64), vd1 = __shfl(dv, i1, 64), vd2 = __shfl(dv, i2, 64);
-
-    int nsub = allin ? 1 : 0;
-    Poly poly;
-    poly.n = 0;
-    if (cmask) {
-        const float X0 = __shfl(X, i0, 64), Y0 = __shfl(Y, i0, 64), Z0 = __shfl(Z, i0, 64);
-        const float X1 = __shfl(X, i1, 64), Y1 = __shfl(Y, i1, 64), Z1 = __shfl(Z, i1, 64);
-        const float X2 = __shfl(X, i2, 64), Y2 = __shfl(Y, i2, 64), Z2 = __shfl(Z, i2, 64);
-        if (clipped) {
-            poly.n = 3;
-            poly.X[0] = X0; poly.Y[0] = Y0; poly.Z[0] = Z0;
-            poly.X[1] = X1; poly.Y[1] = Y1; poly.Z[1] = Z1;
-            poly.X[2] = X2; poly.Y[2] = Y2; poly.Z[2] = Z2;
-            clip_polygon(poly, c.pj.near_m);
-            nsub = poly.n >= 3 ? poly.n - 2 : 0;
-        }
-    }
-    const int maxsub = cmask ? wave_max(nsub) : 1;
-    for (int s = 0; s < maxsub; ++s) {
+    // the clipped triangles first, eight at a time (a lane per triangle of their
+    // polygons' fans), then those inside the guard band (lane = triangle)
+    uint64_t rest = cmask;
+    for (;;) {
+        const bool clip = rest != 0;
         Setup S = {};
         int ok = 0;
-        if (s < nsub) {
-            if (allin) {
-                ok = setup_triangle(vx0, vy0, vd0, vx1, vy1, vd1, vx2, vy2, vd2, c.rx0, c.ry0, c.R, S);
-            } else {
-                int ax, ay, bx, by, cx2, cy2;
-                float ad, bd, cd;
-                project(c.pj, poly.X[0], poly.Y[0], poly.Z[0], ax, ay, ad);
-                project(c.pj, poly.X[s + 1], poly.Y[s + 1], poly.Z[s + 1], bx, by, bd);
-                project(c.pj, poly.X[s + 2], poly.Y[s + 2], poly.Z[s + 2], cx2, cy2, cd);
-                ok = setup_triangle(ax, ay, ad, bx, by, bd, cx2, cy2, cd, c.rx0, c.ry0, c.R, S);
-            }
+        uint32_t id = myid;
+        int ax, ay, bx, by, cx, cy;
+        float ad, bd, cd;
+        bool draw;
+        if (clip) {
+            float pX = X, pY = Y, pZ = Z, pd = 0.f;
+            int n, src, px = 0, py = 0;
+            clip_group(rest, packed, lane, c.pj.near_m, pX, pY, pZ, n, src);
+            const int v = lane & 7;
+            if (v < n) project(c.pj, pX, pY, pZ, px, py, pd);
+            const int l0 = lane & 56, l1 = (lane + 1) & 63, l2 = (lane + 2) & 63;
+            ax = __shfl(px, l0, 64); ay = __shfl(py, l0, 64); ad = __shfl(pd, l0, 64);
+            bx = __shfl(px, l1, 64); by = __shfl(py, l1, 64); bd = __shfl(pd, l1, 64);
+            cx = __shfl(px, l2, 64); cy = __shfl(py, l2, 64); cd = __shfl(pd, l2, 64);
+            draw = v + 2 < n;
+            id = d.first + (uint32_t)src;
+        } else {
+            ax = __shfl(xi, i0, 64); ay = __shfl(yi, i0, 64); ad = __shfl(dv, i0, 64);
+            bx = __shfl(xi, i1, 64); by = __shfl(yi, i1, 64); bd = __shfl(dv, i1, 64);
+            cx = __shfl(xi, i2, 64); cy = __shfl(yi, i2, 64); cd = __shfl(dv, i2, 64);
+            draw = allin;
         }
+        if (draw) ok = setup_triangle(ax, ay, ad, bx, by, bd, cx, cy, cd, c.rx0, c.ry0, c.R, S);
         bool big = false, bal = false;
         int npx = 0;
         if (ok) {
             npx = (S.px1 - S.px0 + 1) * (S.py1 - S.py0 + 1);
-            if (npx <= c.lane_max) raster_small(S, myid, c.rx0, c.ry0, c.P, zb);
+            if (npx <= c.lane_max) raster_small(S, id, c.rx0, c.ry0, c.P, zb);
             else if (npx <= c.small_max) bal = true;
             else big = true;
         }
@@ -1117,8 +1158,8 @@ __device__ void draw_cluster(const Ctx &c, const ClusterData &d, int lane, const
             const int tot = wave_incl_sum(npx, lane);
             stat_add(stats, kStatCandPixels, lane, (uint64_t)__builtin_amdgcn_readlane(tot, 63));
         }
-        if (kBin && c.binning) bin_wave(c, S, myid, lane, bal);
-        if (__ballot(bal)) raster_balanced(S, myid, bal, lane, c.rx0, c.ry0, c.P, c.own, zb);
+        if (kBin && c.binning) bin_wave(c, S, id, lane, bal);
+        if (__ballot(bal)) raster_balanced(S, id, bal, lane, c.rx0, c.ry0, c.P, c.own, zb);
         bool spill = false;
         if (big) {
             const int slot = atomicAdd(c.nbig, 1);
@@ -1132,7 +1173,7 @@ __device__ void draw_cluster(const Ctx &c, const ClusterData &d, int lane, const
                 r.q0 = S.q0;
                 r.q1 = S.q1;
                 r.q2 = S.q2;
-                r.id = myid;
+                r.id = id;
             } else {
                 spill = true;
             }
@@ -1141,9 +1182,10 @@ __device__ void draw_cluster(const Ctx &c, const ClusterData &d, int lane, const
         while (bmask) {
             const int L = __ffsll((unsigned long long)bmask) - 1;
             bmask &= bmask - 1;
-            const TriRec t = lane_record(S, myid, L);
+            const TriRec t = lane_record(S, id, L);
             raster_tiles(t, t.py0 >> 3, t.py1 >> 3, lane, c.ry0, c.rx0, c.P, zb);
         }
+        if (!clip) break;
     }
 }
 
