@@ -297,7 +297,8 @@ int gal_step(gal_batch *b, const float *actions_dev, const gal_outputs *out, voi
  *  prologue   clusters drawn before the first occlusion test (>= 0)
  *  persistent 1 = one persistent raster kernel whose workgroups drain the
  *             (env, region) work queue, longest items first; 0 = one
- *             workgroup per item
+ *             workgroup per item (more items than are resident at once are
+ *             started in the order of their times in the previous step)
  *  robot_lanes lanes per environment in the robot-step kernel: 64 (one env
  *             per wave) or 32 (two envs per wave)
  *  graph      1 = gal_step replays the whole step as a captured hipGraph

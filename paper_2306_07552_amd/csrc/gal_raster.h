@@ -62,11 +62,11 @@ struct RasterParams {
     int32_t occlusion; // 1 = cull clusters hidden behind the z-buffer bounds
     int32_t prologue;  // clusters drawn before occlusion culling starts
     int32_t persistent;// 1 = persistent kernel draining the work queue
-    int32_t order;     // 1 = the queue follows the last step's item times, longest first
+    int32_t order;     // 1 = the items follow item_order (the last step's times, longest first)
     int32_t bin;       // 1 = mid-sized triangles are binned per 8x8 tile in LDS and drawn tile by tile
     unsigned long long *stats; // optional work counters [8] (null = off)
     uint32_t *item_cost;        // [work] last time of each work item (wall-clock ticks)
-    const uint32_t *item_order; // [work] queue position -> work item
+    const uint32_t *item_order; // [work] queue or launch position -> work item
 };
 
 hipError_t raster_prepare();   // raises the dynamic-LDS limit of the raster kernels

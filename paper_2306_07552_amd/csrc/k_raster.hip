@@ -1610,6 +1610,31 @@ __device__ __forceinline__ void raster_item(const RenderMesh &m, const RasterPar
     __syncthreads();   // the LDS is reused by the next item
 }
 
+// Queue or launch position i's work item: the order the robot step computed from
+// the last step's item times, or the static order (the position itself).
+__device__ __forceinline__ int item_at(const RasterParams &rp, int i, int num_work)
+{
+    if (!rp.order || !rp.item_order) return i;
+    const int idx = (int)rp.item_order[i];
+    return (unsigned)idx < (unsigned)num_work ? idx : i;
+}
+
+// Work item idx, timed: its time orders the next step's items (raster_item ends
+// with a barrier, so every wave is done).
+template <int kBlock, bool kColor, bool kBin>
+__device__ __forceinline__ void timed_item(const RenderMesh &m, const RasterParams &rp, const float *camera,
+                                           const int32_t *env_res, const uint64_t *env_depth_off,
+                                           const uint32_t *work, int idx, uint32_t *depth, uint8_t *rgb,
+                                           unsigned long long *zdyn, ItemShared<kBlock> &sh)
+{
+    const uint64_t t0 = wall_clock64();
+    raster_item<kBlock, kColor, kBin>(m, rp, camera, env_res, env_depth_off, work[idx], depth, rgb, zdyn, sh);
+    if (threadIdx.x == 0 && rp.item_cost) {
+        const uint64_t dt = wall_clock64() - t0;
+        rp.item_cost[idx] = (uint32_t)(dt < 0xFFFFFFFFull ? dt : 0xFFFFFFFFull);
+    }
+}
+
 // One workgroup per work item.
 // Waves per SIMD the register allocation is sized for: 4 at 512 and 1024
 // threads (two workgroups' or one workgroup's waves per CU); with bins a
@@ -1630,8 +1655,8 @@ __global__ __launch_bounds__(kBlock, (raster_waves_per_eu<kBlock, kBin>())) void
 {
     extern __shared__ __attribute__((aligned(16))) unsigned long long zdyn[];
     __shared__ ItemShared<kBlock> sh;
-    raster_item<kBlock, kColor, kBin>(m, rp, camera, env_res, env_depth_off, work[blockIdx.x], depth, rgb,
-                                zdyn, sh);
+    timed_item<kBlock, kColor, kBin>(m, rp, camera, env_res, env_depth_off, work,
+                                     item_at(rp, (int)blockIdx.x, num_work), depth, rgb, zdyn, sh);
 }
 
 // Persistent: as many workgroups as fit on the chip drain the work queue
@@ -1652,21 +1677,8 @@ __global__ __launch_bounds__(kBlock, (raster_waves_per_eu<kBlock, kBin>())) void
         const int i = sh.queue_item;
         __syncthreads();
         if (i >= num_work) break;
-        // the queue position's work item (static order: the position itself)
-        int idx = i;
-        if (rp.order && rp.item_order) {
-            idx = (int)rp.item_order[i];
-            if ((unsigned)idx >= (unsigned)num_work) idx = i;
-        }
-        const uint64_t t0 = wall_clock64();
-        raster_item<kBlock, kColor, kBin>(m, rp, camera, env_res, env_depth_off, work[idx], depth, rgb, zdyn,
-                                    sh);
-        // the item's time, which orders the next step's queue (raster_item
-        // ends with a barrier, so every wave is done)
-        if (threadIdx.x == 0 && rp.item_cost) {
-            const uint64_t dt = wall_clock64() - t0;
-            rp.item_cost[idx] = (uint32_t)(dt < 0xFFFFFFFFull ? dt : 0xFFFFFFFFull);
-        }
+        timed_item<kBlock, kColor, kBin>(m, rp, camera, env_res, env_depth_off, work, item_at(rp, i, num_work), depth,
+                                         rgb, zdyn, sh);
     }
 }
 
