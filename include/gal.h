@@ -280,9 +280,11 @@ int gal_step(gal_batch *b, const float *actions_dev, const gal_outputs *out, voi
  * batch renderer of Section 3.1; not in the paper).  Every setting produces
  * the same bits (the outputs are defined independently of how the work is split); the
  * settings only change speed, and an autotuner picks among them.
- *  block      threads per workgroup: 256, 512 or 1024
+ *  block      threads per workgroup: 256, 512 or 1024 (512: 1024 where at most
+ *             one workgroup per CU can be, or needs to be, in flight)
  *  region     square pixel region owned by one workgroup: 32, 64 or 128 (must
- *             divide every env resolution above it)
+ *             divide every env resolution above it); a batch with no more
+ *             regions than CUs has them halved once, with half as many twice
  *  lane_max   triangles whose clipped pixel bbox has at most this many pixels
  *             are rasterised by their own lane (0..4096)
  *  small_max  larger ones up to this many pixels are rasterised together by

@@ -236,6 +236,7 @@ struct gal_batch {
     int64_t n_clusters = 0, n_cverts = 0, n_tris = 0;
     unsigned long long *d_stats = nullptr;  // raster work counters (allocated on demand)
     std::vector<int64_t> cl_count_host;    // clusters per env
+    int64_t clusters = 0;                  // of all envs
     int32_t work_cap = 0;
     uint32_t *d_queue = nullptr;            // persistent raster work-queue counter
     // surrogate pre-filter
@@ -249,7 +250,10 @@ struct gal_batch {
     uint64_t *d_occ_off = nullptr;
     int32_t *d_occ_dims = nullptr;
     int32_t occ_max_cells = 0;
-    int32_t persist_grid = 0;
+    int32_t num_cus = 0;
+    int32_t halvings = 0;       // of every region's side, in a batch of few items (set_halvings)
+    int32_t item_region = 0;    // largest region side of a work item
+    int32_t resident[2] = {};   // raster workgroups resident at once, depth alone / with colour
     int32_t robot_lanes = 64;
     int32_t use_graph = 0;
     int32_t split = 0;   // cheapest envs rendered with halved regions
@@ -304,19 +308,55 @@ namespace {
 int enqueue_step(gal_batch *b, const float *actions_dev, const gal_outputs *out, hipStream_t s,
                  hipEvent_t *ev);
 
-// Region side of env e's items: the tuned region (or the resolution, if
-// smaller), halved for the `split` cheapest envs when it stays a multiple of 8.
-int item_region(const gal_batch *b, int e, bool half)
+// Region side of env e's items, the tuned region (or the resolution, if
+// smaller) halved *h times: the batch's own halvings, then once more for the
+// `split` cheapest envs; a side that is not a multiple of 16 stays.
+int item_region(const gal_batch *b, int e, bool half, uint32_t *h)
 {
-    const int R = std::min(b->res_host[e], b->rast.region);
-    return (half && R % 16 == 0) ? R / 2 : R;
+    int R = std::min(b->res_host[e], b->rast.region);
+    *h = 0;
+    const auto halve = [&](bool want) {
+        if (!want || R % 16 != 0) return;
+        R /= 2;
+        ++*h;
+    };
+    halve(b->halvings >= 1 && R > 64);
+    halve(b->halvings >= 2 && R > 32);
+    halve(half);
+    return R;
+}
+
+// A batch of few items leaves CUs idle while each item is drawn by one
+// workgroup, so its regions are halved: those above 64 pixels where there are no
+// more items than CUs, then those above 32 where there is still less than one
+// item for two CUs.  The geometry work of a region does not fall with its area,
+// so more items than that cost more than the idle CUs give.  Steps with regions
+// of 128, 64 and 32 pixels: 256 apartments 111, 98 and 217 us; 64 of them 95, 70
+// and 69; 16 of them 89, 67 and 52; rooms at 64 pixels, 64 and 32: 128 of them
+// 48 and 43, 256 of them 49 and 59.
+void set_halvings(gal_batch *b)
+{
+    const auto items = [&]() {
+        int64_t n = 0;
+        for (int e = 0; e < b->N; ++e) {
+            uint32_t h;
+            const int r = b->res_host[e], R = item_region(b, e, false, &h);
+            n += (int64_t)(r / R) * (r / R);
+        }
+        return n;
+    };
+    b->halvings = 0;
+    if (items() > b->num_cus) return;
+    b->halvings = 1;
+    if (items() <= b->num_cus / 2) b->halvings = 2;
 }
 
 // (env, region) work items, longest envs first (so the tail of the launch is
 // short), regions of one env 8 items apart (same XCD, shared L2).  Item word:
-// env (bits 0..19), region index (20..30), halved region (31).
+// env (bits 0..19), region index (20..29), halvings of the region side (30..31).
 int build_work(gal_batch *b)
 {
+    set_halvings(b);
     const int N = b->N;
     std::vector<int32_t> order(N);
     for (int e = 0; e < N; ++e) order[e] = e;
@@ -326,22 +366,25 @@ int build_work(gal_batch *b)
         return ca > cc;
     });
     std::vector<uint32_t> work;
+    b->item_region = 8;
     const int first_half = N - std::min(std::max(b->split, 0), N);
     for (int g = 0; g < N; g += 8) {
         int maxreg = 0;
         for (int k = g; k < std::min(N, g + 8); ++k) {
             const int r = b->res_host[order[k]];
-            const int R = item_region(b, order[k], k >= first_half);
+            uint32_t h;
+            const int R = item_region(b, order[k], k >= first_half, &h);
             maxreg = std::max(maxreg, (r / R) * (r / R));
         }
         for (int reg = 0; reg < maxreg; ++reg)
             for (int k = g; k < std::min(N, g + 8); ++k) {
                 const int e = order[k];
                 const int r = b->res_host[e];
-                const int R = item_region(b, e, k >= first_half);
-                const uint32_t half = R < std::min(r, b->rast.region) ? 1u : 0u;
-                if (reg < (r / R) * (r / R))
-                    work.push_back((uint32_t)e | ((uint32_t)reg << 20) | (half << 31));
+                uint32_t h;
+                const int R = item_region(b, e, k >= first_half, &h);
+                if (reg >= (r / R) * (r / R)) continue;
+                work.push_back((uint32_t)e | ((uint32_t)reg << 20) | (h << 30));
+                b->item_region = std::max(b->item_region, R);
             }
     }
     if ((int32_t)work.size() > b->work_cap) {
@@ -366,6 +409,18 @@ int build_work(gal_batch *b)
     if (e != hipSuccess) return fail(GAL_EDEVICE, "hipMemcpy(work) failed: %s", hipGetErrorString(e));
     b->rast.item_cost = b->d_item_cost;
     b->rast.item_order = b->d_item_order;
+    return GAL_OK;
+}
+
+// Raster workgroups resident at once with the present tuning and work list.
+int set_resident(gal_batch *b)
+{
+    for (int color = 0; color < 2; ++color) {
+        if (color && !(b->flags & GAL_COLOR)) continue;
+        b->resident[color] = gal::raster_persistent_grid(b->rast, b->item_region, color != 0);
+        if (b->resident[color] <= 0)
+            return fail(GAL_EDEVICE, "occupancy query for the persistent raster kernel failed");
+    }
     return GAL_OK;
 }
 
@@ -448,13 +503,12 @@ int gal_set_tuning(gal_batch *b, const gal_tuning *t)
     b->rast.bin = t->bin;
     b->sb.layer_hint = t->layer_cache ? b->d_layer_hint : nullptr;
     b->tune_gen += 1;
-    b->persist_grid = gal::raster_persistent_grid(b->rast, b->max_res, (b->flags & GAL_COLOR) != 0);
-    if (b->persist_grid <= 0) return fail(GAL_EDEVICE, "occupancy query for the persistent raster kernel failed");
     if (rebuild) {
         HIP_TRY(hipDeviceSynchronize());
-        return build_work(b);
+        const int rc = build_work(b);
+        if (rc) return rc;
     }
-    return GAL_OK;
+    return set_resident(b);
 }
 
 int gal_autotune(gal_batch *b, const float *actions_dev, const gal_outputs *out, void *stream,
@@ -625,7 +679,7 @@ int gal_autotune(gal_batch *b, const float *actions_dev, const gal_outputs *out,
     // noise), with three times the steps, in two interleaved rounds, each
     // candidate keeping its best.
     if (result == GAL_OK && (result = gal_set_tuning(b, &best_c)) == GAL_OK) {
-        const int slots = b->persist_grid;
+        const int slots = b->resident[(b->flags & GAL_COLOR) ? 1 : 0];
         const gal_tuning w = best_c;
         std::vector<gal_tuning> c2;
         for (int flip : {0, 1})
@@ -1089,6 +1143,7 @@ int gal_create_batch(const gal_config *cfg, const gal_robot *robot, const gal_sc
         b->n_clusters = (int64_t)cl_off[N];
         b->cl_count_host.resize(N);
         for (int e = 0; e < N; ++e) b->cl_count_host[e] = (int64_t)(cl_off[e + 1] - cl_off[e]);
+        b->clusters = (int64_t)cl_off[N];
         b->n_cverts = (int64_t)nv_tot;
         b->n_tris = (int64_t)nt_tot;
         if (cfg->flags & GAL_COLOR) {
@@ -1144,12 +1199,15 @@ int gal_create_batch(const gal_config *cfg, const gal_robot *robot, const gal_sc
         std::vector<uint64_t> doff(N + 1);
         for (int e = 0; e <= N; ++e) doff[e] = (uint64_t)b->depth_off_host[e];
         HIP_TRY(hipMemcpy(b->d_depth_off, doff.data(), sizeof(uint64_t) * (N + 1), hipMemcpyHostToDevice));
+        int dev = 0;
+        HIP_TRY(hipGetDevice(&dev));
+        HIP_TRY(hipDeviceGetAttribute(&b->num_cus, hipDeviceAttributeMultiprocessorCount, dev));
         if ((rc = build_work(b))) return cleanup(rc);
         HIP_TRY(gal::raster_prepare());
         b->rast.persistent = 0;
         if ((rc = b->mem.alloc(&b->d_queue, 1))) return cleanup(rc);
         HIP_TRY(hipMemset(b->d_queue, 0, sizeof(uint32_t)));
-        b->persist_grid = gal::raster_persistent_grid(b->rast, b->max_res, (cfg->flags & GAL_COLOR) != 0);
+        if ((rc = set_resident(b))) return cleanup(rc);
         HIP_TRY(hipStreamCreateWithFlags(&b->cap_stream, hipStreamNonBlocking));
     }
 
@@ -1266,16 +1324,29 @@ int enqueue_step(gal_batch *b, const float *actions_dev, const gal_outputs *out,
     // goes by says little about an item's time (correlation 0.2), so the last
     // workgroups to start are often long ones (1024 apartments: the launch takes
     // 226 us in the static order, the step 247 us, and 193 in this one)
-    const bool by_time = b->rast.persistent ? b->rast.order != 0 : b->num_work > b->persist_grid;
-    const bool order_items = out->depth && by_time && b->num_work <= gal::kOrderCap;
     gal::RasterParams rast = b->rast;
+    int slots = b->resident[out->rgb ? 1 : 0];
+    // 1024 threads for 512, one workgroup per CU for two: where the z-buffer
+    // (with colour) leaves LDS for no second one, and up to two items per CU, all
+    // in flight at once either way but then sharing their CU unevenly; there only
+    // with clusters enough for the waves.  512 and 1024 threads: 512 with colour
+    // 229 and 174 us; 512 apartments 156 and 134, 600 of them 148 and 148, 768 of
+    // them 153 and 181; 256 uneven scenes (512 items) 183 and 146; 128 one-room
+    // scenes (512 items, 10 clusters each) 42 and 51.
+    const bool many = b->clusters >= 64 * (int64_t)b->N;
+    if (rast.block == 512 && !rast.bin && (slots <= b->num_cus || (many && b->num_work <= 2 * b->num_cus))) {
+        rast.block = 1024;
+        slots = b->num_cus;
+    }
+    const bool by_time = rast.persistent ? rast.order != 0 : b->num_work > slots;
+    const bool order_items = out->depth && by_time && b->num_work <= gal::kOrderCap;
     rast.order = order_items ? 1 : 0;
     const gal::ItemOrder ord{b->d_item_cost, order_items ? b->num_work : 0, b->d_item_order};
     HIP_TRY(gal::launch_robot_step(b->rp, sb, actions_dev, so, b->d_queue, b->robot_lanes, ord, s));
     if (ev) HIP_TRY(hipEventRecord(ev[2], s));
     if (out->depth)
         HIP_TRY(gal::launch_raster(b->mesh, rast, b->sb.camera, b->d_res, b->d_depth_off, b->d_work,
-                                   b->num_work, b->max_res, b->d_queue, b->persist_grid, out->depth,
+                                   b->num_work, b->item_region, b->d_queue, slots, out->depth,
                                    out->rgb, s));
     if (ev) HIP_TRY(hipEventRecord(ev[3], s));
     return GAL_OK;

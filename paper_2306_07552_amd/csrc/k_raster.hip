@@ -1263,10 +1263,10 @@ __device__ __forceinline__ void raster_item(const RenderMesh &m, const RasterPar
     int &next = sh.next;
     constexpr int kWaves = kBlock / 64;
     const int env = (int)(item & 0xFFFFFu);
-    const int reg = (int)((item >> 20) & 0x7FFu);
+    const int reg = (int)((item >> 20) & 0x3FFu);
     const int res = env_res[env];
     Ctx c;
-    c.R = min(res, rp.region) >> (item >> 31);
+    c.R = min(res, rp.region) >> (item >> 30);
     const int nr = res / c.R;
     c.rx0 = (reg % nr) * c.R;
     c.ry0 = (reg / nr) * c.R;
