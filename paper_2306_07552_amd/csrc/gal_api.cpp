@@ -1147,8 +1147,8 @@ int gal_create_batch(const gal_config *cfg, const gal_robot *robot, const gal_sc
         b->n_cverts = (int64_t)nv_tot;
         b->n_tris = (int64_t)nt_tot;
         if (cfg->flags & GAL_COLOR) {
-            uint8_t *d_rgb;
-            if ((rc = b->mem.alloc(&d_rgb, (size_t)std::max<uint64_t>(nt_tot, 1) * 3))) return cleanup(rc);
+            uint8_t *d_rgb;   // (the colour arrays are read by words)
+            if ((rc = b->mem.alloc(&d_rgb, (size_t)nt_tot * 3 + 4))) return cleanup(rc);
             HIP_TRY(hipMemcpy(d_rgb, sc->tri_rgb, nt_tot * 3, hipMemcpyHostToDevice));
             b->mesh.tri_rgb = d_rgb;
         }
@@ -1160,7 +1160,7 @@ int gal_create_batch(const gal_config *cfg, const gal_robot *robot, const gal_sc
             b->mesh.link_frames = b->sb.link_frames;
             if ((cfg->flags & GAL_COLOR) && robot->link_rgb) {
                 uint8_t *d_lrgb;
-                if ((rc = b->mem.alloc(&d_lrgb, (size_t)8 * 3))) return cleanup(rc);
+                if ((rc = b->mem.alloc(&d_lrgb, (size_t)8 * 3 + 4))) return cleanup(rc);
                 HIP_TRY(hipMemcpy(d_lrgb, robot->link_rgb, 8 * 3, hipMemcpyHostToDevice));
                 b->mesh.link_rgb = d_lrgb;
             }
@@ -1171,7 +1171,7 @@ int gal_create_batch(const gal_config *cfg, const gal_robot *robot, const gal_sc
             b->mesh.num_objects = b->O;
             if ((cfg->flags & GAL_COLOR) && sc->obj_rgb) {
                 uint8_t *d_orgb;
-                if ((rc = b->mem.alloc(&d_orgb, (size_t)N * b->O * 3))) return cleanup(rc);
+                if ((rc = b->mem.alloc(&d_orgb, (size_t)N * b->O * 3 + 4))) return cleanup(rc);
                 HIP_TRY(hipMemcpy(d_orgb, sc->obj_rgb, (size_t)N * b->O * 3, hipMemcpyHostToDevice));
                 b->mesh.obj_rgb = d_orgb;
             }
