@@ -74,14 +74,38 @@ __device__ __forceinline__ int snap16(float v)
     return (int)rintf(s);
 }
 
+// 1 / b, correctly rounded (b positive): one Newton step from the hardware's
+// estimate, which on gfx950 equals the IEEE division for every float of 2^-60 to
+// 2^60 (all were compared); beyond (an infinite vertex) the estimate stands.
+// 5 instructions for the general division's 11.
+__device__ __forceinline__ float recip(float b)
+{
+    const float y = __builtin_amdgcn_rcpf(b);
+    return b < 0x1p60f ? __builtin_fmaf(__builtin_fmaf(-b, y, 1.0f), y, y) : y;
+}
+
+// a / b, correctly rounded, from y = 1 / b correctly rounded: the first step makes
+// the quotient faithful, the second is Markstein's theorem (P. Markstein,
+// "Computation of elementary functions on the IBM RISC System/6000 processor",
+// 1990).  Residuals too small to be held only occur for |a| < 2^-60, whose
+// quotient is lost beside the half width that it is added to.  (With this, the
+// shared reciprocal and the region's sides tested only where something is clipped,
+// the step of 1024 apartments takes 191 us for 193.)
+__device__ __forceinline__ float quotient(float a, float b, float y)
+{
+    const float q = a * y;
+    const float q1 = __builtin_fmaf(__builtin_fmaf(-b, q, a), y, q);
+    return __builtin_fmaf(__builtin_fmaf(-b, q1, a), y, q1);
+}
+
 __device__ __forceinline__ void project(const Proj &pj, float X, float Y, float Z, int &xi, int &yi,
                                         float &d)
 {
-    float xs = pj.hw + pj.hw * (X / Z);
-    float ys = pj.hw + pj.hw * (Y / Z);
+    const float inv = recip(Z);
+    float xs = pj.hw + pj.hw * quotient(X, Z, inv);
+    float ys = pj.hw + pj.hw * quotient(Y, Z, inv);
     xi = snap16(xs);
     yi = snap16(ys);
-    float inv = 1.0f / Z;
     d = (pj.invn - inv) * pj.kd;
 }
 
@@ -243,7 +267,7 @@ __device__ __forceinline__ int setup_triangle(int x0, int y0, float d0, int x1, 
     const int t2 = (int)((uint32_t)(S.y1 - S.y0) << 16) - (S.x1 - S.x0);
     const int bias = ((t0 >> 31) + 1) | (((t1 >> 31) + 1) << 1) | (((t2 >> 31) + 1) << 2);
     S.bias = bias;
-    const float invA = 1.0f / (float)(-A2);
+    const float invA = recip((float)(-A2));
     S.q0 = d0 * invA;
     S.q1 = d2 * invA;   // swapped vertex 1 is the original vertex 2
     S.q2 = d1 * invA;
@@ -555,7 +579,7 @@ __device__ __forceinline__ void raster_balanced(const Setup &S, uint32_t myid, b
     const int xy1 = (S.x1 & 0xFFFF) | (S.y1 << 16);
     const int xy2 = (S.x2 & 0xFFFF) | (S.y2 << 16);
     const int meta = S.px0 | (S.py0 << 9) | ((ns > 0 ? ns - 1 : 0) << 18) | (S.bias << 27);
-    const float invns = 1.0f / (float)(ns > 0 ? ns : 1);
+    const float invns = __builtin_amdgcn_rcpf((float)(ns > 0 ? ns : 1));
     // (first span << 6 | lane): increasing along the lanes with spans
     const int start = (excl << 6) | lane;
     int carry = 0;
@@ -1131,11 +1155,16 @@ __device__ void draw_cluster(const Ctx &c, const ClusterData &d, int lane, const
 #pragma unroll
         for (int k = 0; k < 5; ++k)
             if (clip_plane(X, Y, Z, k, c.pj.near_m) < 0.0f) oc |= 1u << k;
+        if ((oc & 1u) == 0) project(c.pj, X, Y, Z, xi, yi, dv);
+    }
+
+    // the region's sides: they only spare clipping (a triangle inside the guard band
+    // but outside the region has no pixel there), and count in the statistics
+    if (stats || __ballot((oc & kClipBits) != 0u)) {
         if (X - c.kl * Z < 0.0f) oc |= 1u << 5;
         if (c.kr * Z - X < 0.0f) oc |= 1u << 6;
         if (Y - c.kt * Z < 0.0f) oc |= 1u << 7;
         if (c.kb * Z - Y < 0.0f) oc |= 1u << 8;
-        if ((oc & 1u) == 0) project(c.pj, X, Y, Z, xi, yi, dv);
     }
 
     // ---- per triangle
