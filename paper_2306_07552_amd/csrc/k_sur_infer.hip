@@ -3,7 +3,7 @@
 // learned pre-filter in front of the static-scene overlap test of the
 // kinematic step (Section 3.2 of the paper describes the exact test).
 //
-// A tile of 32 rows (two 16-row MFMA tiles) is served by `splits` workgroups
+// A tile of 32 rows (two 16-row MFMA tiles), or two tiles, is served by `splits` workgroups
 // (1, 2, 4 or 8) that share the first layer's K = 2112 inputs, cut into 8
 // chunks: chunk 0 = the 64 scalar inputs and patch columns 0..31 (10 K-steps
 // of 32), chunk c >= 1 = patch columns 32c..32c+31 (8 K-steps).  A workgroup
@@ -177,23 +177,30 @@ struct RowInfo {
     bool live;
 };
 
-template <int FEAT>
+// kM: 16-row MFMA tiles per workgroup, one 32-row tile or (input rows given,
+// several splits) two of them.  A workgroup streams its chunks' weights, 270 KB of
+// 1.08 MB at 4 splits, whatever its rows, and 26 bytes per clock reach a CU; so
+// where the 32-row tiles and their splits are more workgroups than CUs, 64 rows
+// halve what is streamed and still leave one workgroup per CU.  The splits stay
+// those of the 32-row tiles, and so do the sums.  4096 rows: the first layer 16 us with
+// 32-row tiles, 12.7 so (with rows requested a chunk ahead), the call 25.4 and 22.
+template <int FEAT, int kM>
 __global__ __launch_bounds__(kThreads) void k_sur_l1(SurInferArgs p)
 {
-    __shared__ __attribute__((aligned(16))) uint16_t lds[2 * kR * kHPitch];
-    __shared__ RowInfo rows[kR];
-    __shared__ float zs[kR];
+    constexpr bool kPair = kM == 4;
+    static_assert(kM == 2 || (kPair && FEAT == 0), "one tile, or two of given rows");
+    __shared__ __attribute__((aligned(16))) uint16_t lds[kPair ? 16 * kM * kAPitch : 2 * kR * kHPitch];
+    __shared__ RowInfo rows[FEAT ? kR : 1];
+    __shared__ float zs[kPair ? 1 : kR];
     static_assert(kR * kAPitch <= 2 * kR * kHPitch, "chunk fits the activation buffer");
     uint16_t(*A)[kAPitch] = reinterpret_cast<uint16_t(*)[kAPitch]>(lds);
-    uint16_t(*H)[kR][kHPitch] = reinterpret_cast<uint16_t(*)[kR][kHPitch]>(lds);
-
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int S = p.splits;
     // Workgroups are handed to the 8 XCDs in turn (blockIdx mod 8).  When the
     // tile count allows, all splits of tile t go to XCD t mod 8, where the
     // second launch's workgroup t runs: its partial sums are then read from
     // the same L2 they were written to.
-    const int tiles_all = gridDim.x / S;
+    const int tiles_all = gridDim.x / S;   // (pairs of tiles with kPair)
     int tile, split;
     if (S > 1 && tiles_all % 8 == 0) {
         const int slot = blockIdx.x >> 3;
@@ -203,14 +210,22 @@ __global__ __launch_bounds__(kThreads) void k_sur_l1(SurInferArgs p)
         tile = blockIdx.x / S;
         split = blockIdx.x - tile * S;
     }
+    // a pair is tiles 16 g + x and 16 g + x + 8 (both of XCD x), or adjacent tiles
+    int tile2 = 0;
+    if (kPair) {
+        const int pr = tile;
+        const bool far = tiles_all % 8 == 0;
+        tile = far ? 16 * (pr >> 3) + (pr & 7) : 2 * pr;
+        tile2 = far ? tile + 8 : tile + 1;
+    }
     const int row0 = tile * kR;
     const int r16 = lane & 15, kq = (lane >> 4) * 8;
     const int cpb = kChunks / S;
     const int cbeg = split * cpb;
 
-    floatx4 acc[2][2];
+    floatx4 acc[kM][2];
 #pragma unroll
-    for (int m = 0; m < 2; ++m)
+    for (int m = 0; m < kM; ++m)
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[m][j] = floatx4{0.f, 0.f, 0.f, 0.f};
     // this wave's weight fragments of chunk c: column 32 wave + 16 j + r16,
@@ -247,6 +262,24 @@ __global__ __launch_bounds__(kThreads) void k_sur_l1(SurInferArgs p)
         roy = p.og.occ_dims[2 * e + 1];
         roff = p.og.occ_off[e];
     }
+    // the chunk's columns of the given input rows, 16 bytes per thread and pass,
+    // requested before the chunk's weights and while the chunk before is multiplied
+    constexpr int kPasses = FEAT ? 1 : (16 * kM * kChunk0 * 4 + kThreads - 1) / kThreads;
+    typedef uint32_t quad __attribute__((ext_vector_type(4)));
+    quad xin[kPasses];
+    auto load_rows = [&](int c) {
+        const int s0 = c == 0 ? 0 : kChunk0 + kChunkN * (c - 1);
+        const int per_row = (c == 0 ? kChunk0 : kChunkN) * 4;
+#pragma unroll
+        for (int k = 0; k < kPasses; ++k) {
+            const int i = min(tid + k * kThreads, 16 * kM * per_row - 1);
+            const int r = i / per_row, q = i - r * per_row;
+            const int e = (r < kR ? row0 : (tile2 - 1) * kR) + r;
+            const quad v = *reinterpret_cast<const quad *>(p.x + (size_t)min(e, p.rows - 1) * kMlpIn + 32 * s0 + 8 * q);
+            xin[k] = e < p.rows ? v : quad{0u, 0u, 0u, 0u};
+        }
+    };
+    if (FEAT == 0) load_rows(cbeg);
     load_chunk(cbeg);
     if (FEAT) {
         if (tid < kR) {
@@ -266,17 +299,14 @@ __global__ __launch_bounds__(kThreads) void k_sur_l1(SurInferArgs p)
     }
 
     for (int c = cbeg; c < cbeg + cpb; ++c) {
-        const int s0 = c == 0 ? 0 : kChunk0 + kChunkN * (c - 1);
         const int ns = c == 0 ? kChunk0 : kChunkN;
         if (FEAT == 0) {
-            // the chunk's columns of the input rows, 16 bytes per thread and pass
             const int per_row = ns * 4;
-            for (int i = tid; i < kR * per_row; i += kThreads) {
+#pragma unroll
+            for (int k = 0; k < kPasses; ++k) {
+                const int i = tid + k * kThreads;
                 const int r = i / per_row, q = i - r * per_row;
-                const int e = row0 + r;
-                uint4 v = make_uint4(0u, 0u, 0u, 0u);
-                if (e < p.rows) v = *reinterpret_cast<const uint4 *>(p.x + (size_t)e * kMlpIn + 32 * s0 + 8 * q);
-                *reinterpret_cast<uint4 *>(&A[r][8 * q]) = v;
+                if (i < 16 * kM * per_row) *reinterpret_cast<quad *>(&A[r][8 * q]) = xin[k];
             }
         } else {
             // chunk 0: wave 1 builds the 64 scalars of the 32 rows (one lane
@@ -345,11 +375,12 @@ __global__ __launch_bounds__(kThreads) void k_sur_l1(SurInferArgs p)
             }
         }
         __syncthreads();
+        if (FEAT == 0 && c + 1 < cbeg + cpb) load_rows(c + 1);
 #pragma unroll
         for (int st = 0; st < kChunk0; ++st) {
             if (st < ns) {
 #pragma unroll
-                for (int m = 0; m < 2; ++m) {
+                for (int m = 0; m < kM; ++m) {
                     const bf16x8 a = *reinterpret_cast<const bf16x8 *>(&A[16 * m + r16][32 * st + kq]);
 #pragma unroll
                     for (int j = 0; j < 2; ++j)
@@ -363,32 +394,40 @@ __global__ __launch_bounds__(kThreads) void k_sur_l1(SurInferArgs p)
 
     // lane holds rows 16 m + 4 (lane / 16) + i, column 32 wave + 16 j + r16
     if (S > 1) {
-        float *mine = p.part + (size_t)(tile * S + split) * kR * kMlpHidden;
+        const int ntiles = (p.rows + kR - 1) / kR;
 #pragma unroll
-        for (int m = 0; m < 2; ++m)
+        for (int m = 0; m < kM; ++m) {
+            const int t = m < 2 ? tile : tile2;
+            if (t >= ntiles) break;   // (the last pair of an odd number of tiles)
+            float *mine = p.part + (size_t)(t * S + split) * kR * kMlpHidden;
 #pragma unroll
             for (int j = 0; j < 2; ++j)
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    mine[(16 * m + 4 * (lane >> 4) + i) * kMlpHidden + kColsW * wave + 16 * j + r16] = acc[m][j][i];
+                    mine[(16 * (m & 1) + 4 * (lane >> 4) + i) * kMlpHidden + kColsW * wave + 16 * j + r16] =
+                        acc[m][j][i];
+        }
         return;
     }
-    // one split: the first hidden layer (bias, ReLU, BF16), then the rest
-    bf16x8 f2[kMlpHidden / 32][2], f3[kMlpHidden / 32][2], f4[kMlpHidden / 32][2];
-    load_layer(p.t.w[0], f2);
-    load_layer(p.t.w[1], f3);
-    load_layer(p.t.w[2], f4);
+    if constexpr (!kPair) {
+        // one split: the first hidden layer (bias, ReLU, BF16), then the rest
+        uint16_t(*H)[kR][kHPitch] = reinterpret_cast<uint16_t(*)[kR][kHPitch]>(lds);
+        bf16x8 f2[kMlpHidden / 32][2], f3[kMlpHidden / 32][2], f4[kMlpHidden / 32][2];
+        load_layer(p.t.w[0], f2);
+        load_layer(p.t.w[1], f3);
+        load_layer(p.t.w[2], f4);
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int n = kColsW * wave + 16 * j + r16;
-        const float bn = p.t.b0[n];
+        for (int j = 0; j < 2; ++j) {
+            const int n = kColsW * wave + 16 * j + r16;
+            const float bn = p.t.b0[n];
 #pragma unroll
-        for (int m = 0; m < 2; ++m)
+            for (int m = 0; m < 2; ++m)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) H[0][16 * m + 4 * (lane >> 4) + i][n] = to_bf16(relu(acc[m][j][i] + bn));
+                for (int i = 0; i < 4; ++i) H[0][16 * m + 4 * (lane >> 4) + i][n] = to_bf16(relu(acc[m][j][i] + bn));
+        }
+        __syncthreads();
+        tail_layers<kR>(p, row0, H, zs, f2, f3, f4);
     }
-    __syncthreads();
-    tail_layers<kR>(p, row0, H, zs, f2, f3, f4);
 }
 
 // Second launch with several splits: a workgroup per half tile (16 rows)
@@ -543,10 +582,12 @@ hipError_t sur_infer(const SurInferArgs &args, hipStream_t s)
     p.splits = sur_infer_splits(p.rows);
     const int tiles = (p.rows + kR - 1) / kR;
     const dim3 grid((unsigned)(tiles * p.splits));
-    if (p.x)
-        hipLaunchKernelGGL(k_sur_l1<0>, grid, dim3(kThreads), 0, s, p);
+    if (!p.x)
+        hipLaunchKernelGGL((k_sur_l1<1, 2>), grid, dim3(kThreads), 0, s, p);
+    else if (p.splits > 1 && tiles * p.splits > 256)
+        hipLaunchKernelGGL((k_sur_l1<0, 4>), dim3((unsigned)((tiles + 1) / 2 * p.splits)), dim3(kThreads), 0, s, p);
     else
-        hipLaunchKernelGGL(k_sur_l1<1>, grid, dim3(kThreads), 0, s, p);
+        hipLaunchKernelGGL((k_sur_l1<0, 2>), grid, dim3(kThreads), 0, s, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.splits == 1) return e;
     hipLaunchKernelGGL(k_sur_tail, dim3((unsigned)(2 * tiles)), dim3(kThreads), 0, s, p);
