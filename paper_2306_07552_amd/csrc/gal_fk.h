@@ -14,6 +14,17 @@ struct Fk {
     Frame f[8];
 };
 
+// A_j at the angle of sine sq and cosine cq.
+__device__ __forceinline__ Frame joint_frame(const RobotParams &rp, int j, float sq, float cq)
+{
+    const float a = rp.dh[j][0], d = rp.dh[j][1], ca = rp.dh[j][2], sa = rp.dh[j][3];
+    Frame A;
+    A.m[0] = cq;   A.m[1] = -(sq * ca); A.m[2] = sq * sa;     A.m[3] = a * cq;
+    A.m[4] = sq;   A.m[5] = cq * ca;    A.m[6] = -(cq * sa);  A.m[7] = a * sq;
+    A.m[8] = 0.0f; A.m[9] = sa;         A.m[10] = ca;         A.m[11] = d;
+    return A;
+}
+
 __device__ __forceinline__ void forward_kinematics(const RobotParams &rp, const float *st, Fk &out)
 {
     float s, c;
@@ -32,12 +43,7 @@ __device__ __forceinline__ void forward_kinematics(const RobotParams &rp, const 
     for (int j = 0; j < 7; ++j) {
         float sq, cq;
         dsincos(st[3 + j], sq, cq);
-        const float a = rp.dh[j][0], d = rp.dh[j][1], ca = rp.dh[j][2], sa = rp.dh[j][3];
-        Frame A;
-        A.m[0] = cq;   A.m[1] = -(sq * ca); A.m[2] = sq * sa;     A.m[3] = a * cq;
-        A.m[4] = sq;   A.m[5] = cq * ca;    A.m[6] = -(cq * sa);  A.m[7] = a * sq;
-        A.m[8] = 0.0f; A.m[9] = sa;         A.m[10] = ca;         A.m[11] = d;
-        prev = fmul(prev, A);
+        prev = fmul(prev, joint_frame(rp, j, sq, cq));
         out.f[j + 1] = prev;
     }
 }

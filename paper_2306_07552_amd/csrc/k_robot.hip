@@ -2,9 +2,9 @@
 // sphere-proxy collision against the column grid and the object boxes,
 // resolution, episode bookkeeping and the head-camera pose (Galactic,
 // Section 3.2 and Appendix G).  One wave64 (or half-wave) per environment:
-// the chain of seven joint frames is evaluated redundantly by every lane (it
-// is a short serial chain), each lane owns every 64th (32nd) sphere, and the
-// accept/reject decision is a ballot.
+// a lane evaluates one row of the chain of seven joint frames and shares it in
+// LDS, each lane owns every 64th (32nd) sphere, and the accept/reject decision
+// is a ballot.
 #include "gal_fk.h"
 #include "gal_internal.h"
 #include "gal_math.h"
@@ -25,26 +25,94 @@ __device__ __forceinline__ float sanitize(float a, float lim)
     return clampf(a, -lim, lim);
 }
 
-// Frame of `link` (0..7), selected element by element.  Each candidate value
-// passes through an empty asm so that the compiler cannot turn the selects
-// into a load from a selected address, which would keep all eight frames in
-// scratch memory instead of registers.
-__device__ __forceinline__ Frame pick(const Fk &fk, int link)
+__device__ __forceinline__ float rlf(float v, int l)
 {
-    Frame r;
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+
+// Order between a wave's LDS writes and reads of other lanes' words (a wave's LDS
+// operations complete in order; this keeps the compiler from moving them).
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// One env's eight link frames in LDS, three rows each.
+constexpr int kFkRows = 24;
+
+__device__ __forceinline__ Frame pick(const float4 *rows, int link)
+{
+    Frame F;
 #pragma unroll
-    for (int k = 0; k < 12; ++k) {
-        float v = fk.f[0].m[k];
-        asm("" : "+v"(v));
-#pragma unroll
-        for (int j = 1; j < 8; ++j) {
-            float c = fk.f[j].m[k];
-            asm("" : "+v"(c));
-            v = link == j ? c : v;
-        }
-        r.m[k] = v;
+    for (int i = 0; i < 3; ++i) {
+        const float4 v = rows[3 * link + i];
+        F.m[4 * i + 0] = v.x;
+        F.m[4 * i + 1] = v.y;
+        F.m[4 * i + 2] = v.z;
+        F.m[4 * i + 3] = v.w;
     }
-    return r;
+    return F;
+}
+
+// Row (a0 .. a3) of a frame times the frame B, in fmul's order.
+__device__ __forceinline__ float4 row_mul(const float4 &a, const Frame &B)
+{
+    float r[4];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        const float t = a.x * B.m[j] + a.y * B.m[4 + j];
+        r[j] = t + a.z * B.m[8 + j];
+    }
+    float t = a.x * B.m[3] + a.y * B.m[7];
+    t = t + a.z * B.m[11];
+    r[3] = t + a.w;
+    return make_float4(r[0], r[1], r[2], r[3]);
+}
+
+// The frames of pose st (the same in the env's kLanes lanes) into `rows`, with
+// forward_kinematics' operations: lane a takes the sine and cosine of angle a, and
+// as a row of a product needs only that row of its left factor, lanes r, r + 4, ...
+// follow row r (3: row 2 again) of the chain.  Issue of the one wave's instructions
+// is what this costs: every lane evaluating all eight angles and all twelve
+// elements, and selecting a sphere's frame from registers, came to about four
+// times as many and kept 96 registers busy.  The robot kernel of 16 envs 9.6 -> 8.3
+// us, of 256 with manipulation (several poses a step) 26.8 -> 22.9.
+template <int kLanes>
+__device__ __forceinline__ void wave_kinematics(const RobotParams &rp, const float *st, int lane, float4 *rows)
+{
+    const int sub = lane & (kLanes - 1), group = lane & ~(kLanes - 1);
+    // (each value passes through an empty asm so that the compiler cannot turn the
+    // selects into a load from a selected address, with st in scratch memory)
+    float angle = st[2];
+    asm("" : "+v"(angle));
+#pragma unroll
+    for (int j = 0; j < 7; ++j) {
+        float q = st[3 + j];
+        asm("" : "+v"(q));
+        angle = (sub & 7) == j + 1 ? q : angle;
+    }
+    float sl, cl;
+    dsincos(angle, sl, cl);
+    const auto from = [&](float v, int j) { return kLanes == 64 ? rlf(v, j) : __shfl(v, group + j, 64); };
+    const float s = from(sl, 0), c = from(cl, 0);
+    const int r = sub & 3;
+    float4 a = make_float4(r == 0 ? c : r == 1 ? s : 0.0f, r == 0 ? -s : r == 1 ? c : 0.0f, r < 2 ? 0.0f : 1.0f,
+                           r == 0 ? st[0] : r == 1 ? st[1] : 0.0f);
+    wave_lds_fence();
+    if (sub < 3) rows[sub] = a;
+    Frame T;
+    T.m[0] = 1.0f; T.m[1] = 0.0f; T.m[2] = 0.0f;  T.m[3] = rp.mount[0];
+    T.m[4] = 0.0f; T.m[5] = 1.0f; T.m[6] = 0.0f;  T.m[7] = rp.mount[1];
+    T.m[8] = 0.0f; T.m[9] = 0.0f; T.m[10] = 1.0f; T.m[11] = rp.mount[2];
+    a = row_mul(a, T);
+#pragma unroll
+    for (int j = 0; j < 7; ++j) {
+        a = row_mul(a, joint_frame(rp, j, from(sl, j + 1), from(cl, j + 1)));
+        if (sub < 3) rows[3 * (j + 1) + sub] = a;
+    }
+    wave_lds_fence();
 }
 
 // Column-grid test of one sphere centre, split into stages so that the
@@ -318,10 +386,32 @@ __global__ __launch_bounds__(256) void k_robot_step(RobotParams rp, SimBuffers s
     const int half = kLanes == 32 ? (lane >> 5) : 0;
     int env = (int)blockIdx.x * kEnvsPerBlock + (int)threadIdx.x / kLanes;
     if (kLanes == 64) env = __builtin_amdgcn_readfirstlane(env);
+    // with two envs per wave, a half-wave past the end still joins the ballots
+    const bool active = env < sb.num_envs;
+    const bool past = !active;
+    if (past) env = kLanes == 64 ? sb.num_envs - 1 : 0;
+    // everything that does not depend on the kinematics is requested first, before
+    // the barrier below
+    float st[10], act[9];
+#pragma unroll
+    for (int k = 0; k < 10; ++k) st[k] = sb.state[(size_t)env * 10 + k];
+#pragma unroll
+    for (int k = 0; k < 9; ++k) act[k] = actions[(size_t)env * 9 + k];
+    int t = sb.counters[(size_t)env * 2 + 0];
+    int episode = sb.counters[(size_t)env * 2 + 1];
+    const bool held = sb.held ? (sb.held[env] != 0) : false;
+    const GridMeta gm = sb.grid_meta[env];
+    // surrogate routing: 1 = static check skipped (no contact assumed),
+    // 2 = skipped but audited (exact check runs; a contact is a mismatch)
+    const int route = sb.skip_flags ? sb.skip_flags[env] : 0;
+    // each lane owns spheres sub + kLanes * p; two passes p are processed together
+    SphereSlots sl;
+    load_slots<kLanes>(rp, sb, env, held, active, sub, 0, sl);
     // The object records of the workgroup's envs, staged in LDS once: every
     // sphere may test all of them, and read from global memory each test of
     // the chain would wait on a load of its own.
     __shared__ float4 obj_lds[kEnvsPerBlock * kMaxObjects * 2];
+    __shared__ float4 fk_lds[kEnvsPerBlock][kFkRows];
     const int env0 = (int)blockIdx.x * kEnvsPerBlock;
     {
         const int ne = min(kEnvsPerBlock, sb.num_envs - env0);
@@ -330,17 +420,7 @@ __global__ __launch_bounds__(256) void k_robot_step(RobotParams rp, SimBuffers s
         for (int i = (int)threadIdx.x; i < n4; i += 256) obj_lds[i] = src[i];
         __syncthreads();
     }
-    if (kLanes == 64 && env >= sb.num_envs) return;
-    // with two envs per wave, a half-wave past the end still joins the ballots
-    const bool active = env < sb.num_envs;
-    if (!active) env = 0;
-
-    float st[10];
-#pragma unroll
-    for (int k = 0; k < 10; ++k) st[k] = sb.state[(size_t)env * 10 + k];
-    int t = sb.counters[(size_t)env * 2 + 0];
-    int episode = sb.counters[(size_t)env * 2 + 1];
-    const float *act = actions + (size_t)env * 9;
+    if (kLanes == 64 && past) return;
 
     // 1. kinematic update: offsets applied directly to the state
     float cand[10];
@@ -363,20 +443,10 @@ __global__ __launch_bounds__(256) void k_robot_step(RobotParams rp, SimBuffers s
         }
     }
 
-    // 2. forward kinematics of the candidate, sphere tests.  Each lane owns
-    // spheres sub + kLanes * p; two passes p are processed together, and the
-    // sphere records and grid bases of the first two are loaded before the
-    // kinematics (they do not depend on it).
-    const bool held = sb.held ? (sb.held[env] != 0) : false;
-    SphereSlots sl;
-    load_slots<kLanes>(rp, sb, env, held, active, sub, 0, sl);
-    Fk fk;
-    forward_kinematics(rp, cand, fk);
-    const GridMeta gm = sb.grid_meta[env];
+    // 2. forward kinematics of the candidate, sphere tests
+    float4 *fk = fk_lds[(int)threadIdx.x / kLanes];
+    wave_kinematics<kLanes>(rp, cand, lane, fk);
     const float *objs = reinterpret_cast<const float *>(obj_lds) + (active ? env - env0 : 0) * rp.num_objects * 8;
-    // surrogate routing: 1 = static check skipped (no contact assumed),
-    // 2 = skipped but audited (exact check runs; a contact is a mismatch)
-    const int route = sb.skip_flags ? sb.skip_flags[env] : 0;
     bool any = false, any_static = false;
     for (int base = 0; base < rp.num_spheres; base += kSlots * kLanes) {
         GridProbe g[kSlots];
@@ -503,14 +573,14 @@ __global__ __launch_bounds__(256) void k_robot_step(RobotParams rp, SimBuffers s
     }
 
     // 5. frames and camera of the final state
-    if (!accepted || done) forward_kinematics(rp, st, fk);
+    if (!accepted || done) wave_kinematics<kLanes>(rp, st, lane, fk);
     if (sub == 0) {
 #pragma unroll
         for (int k = 0; k < 10; ++k) sb.state[(size_t)env * 10 + k] = st[k];
         sb.counters[(size_t)env * 2 + 0] = t;
         sb.counters[(size_t)env * 2 + 1] = episode;
         float cam[12];
-        write_camera(rp, fk.f[0], cam);
+        write_camera(rp, pick(fk, 0), cam);
 #pragma unroll
         for (int k = 0; k < 12; ++k) sb.camera[(size_t)env * 12 + k] = cam[k];
         if (out.state) {
@@ -541,11 +611,6 @@ __global__ __launch_bounds__(256) void k_robot_step(RobotParams rp, SimBuffers s
 
 // ---- manipulation: grasp / carry / release with snap-to-surface and
 // placing, sliding (Section 3.2 grasping paragraphs, Appendix I) ----------
-
-__device__ __forceinline__ float rlf(float v, int l)
-{
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
-}
 
 // Frame of a resting object: Rz(yaw) about its centre.
 __device__ __forceinline__ Frame object_frame(const float *o)
@@ -622,7 +687,7 @@ __device__ __forceinline__ bool grid_point_contact(const RobotParams &rp, const 
 // words; the x, y of every overlapping sphere centre are summed in sphere
 // order (the same in every lane).
 __device__ __forceinline__ bool manip_pose_contacts(const RobotParams &rp, const SimBuffers &sb,
-                                                    const GridMeta &gm, int env, const Fk &fk,
+                                                    const GridMeta &gm, int env, const float4 *fk,
                                                     int held, const Frame &rel, const float *objs,
                                                     int lane, uint32_t *ms_out, uint32_t *mo_out,
                                                     float &sx, float &sy, int &n)
@@ -632,7 +697,7 @@ __device__ __forceinline__ bool manip_pose_contacts(const RobotParams &rp, const
     Frame Fh;
     const float *eh = nullptr;
     if (held >= 0) {
-        Fh = fmul(fk.f[7], rel);
+        Fh = fmul(pick(fk, 7), rel);
         eh = objs + 8 * held + 3;
     }
     bool any = false;
@@ -871,8 +936,9 @@ __global__ __launch_bounds__(256) void k_robot_step_manip(RobotParams rp, SimBuf
     }
     // 2. overlap test of the candidate (its masks are reported)
     const GridMeta gm = sb.grid_meta[env];
-    Fk fk;
-    forward_kinematics(rp, cand, fk);
+    __shared__ float4 fk_lds[4][kFkRows];
+    float4 *fk = fk_lds[(int)threadIdx.x / 64];
+    wave_kinematics<64>(rp, cand, lane, fk);
     float sx, sy;
     int n;
     uint32_t *ms_out = out.contact_static ? out.contact_static + (size_t)env * rp.contact_words : nullptr;
@@ -894,7 +960,7 @@ __global__ __launch_bounds__(256) void k_robot_step_manip(RobotParams rp, SimBuf
             if (!(vn > 1e-6f)) break;
             cand[0] = cand[0] + rp.slide_step * (vx / vn);
             cand[1] = cand[1] + rp.slide_step * (vy / vn);
-            forward_kinematics(rp, cand, fk);
+            wave_kinematics<64>(rp, cand, lane, fk);
             if (!manip_pose_contacts(rp, sb, gm, env, fk, held, rel, objs, lane, nullptr, nullptr, sx,
                                      sy, n)) {
 #pragma unroll
@@ -905,10 +971,10 @@ __global__ __launch_bounds__(256) void k_robot_step_manip(RobotParams rp, SimBuf
         }
     }
     // 4. grasp / release at the resolved pose
-    forward_kinematics(rp, st, fk);
+    wave_kinematics<64>(rp, st, lane, fk);
     if (grasp && held < 0) {
         float tx, ty, tz;
-        fpoint(fk.f[7], rp.grasp_tip[0], rp.grasp_tip[1], rp.grasp_tip[2], tx, ty, tz);
+        fpoint(pick(fk, 7), rp.grasp_tip[0], rp.grasp_tip[1], rp.grasp_tip[2], tx, ty, tz);
         const float r2 = rp.grasp_radius * rp.grasp_radius;
         unsigned long long key = ~0ull;
         if (lane < O) {
@@ -926,11 +992,11 @@ __global__ __launch_bounds__(256) void k_robot_step_manip(RobotParams rp, SimBuf
         }
         if (hi != 0xFFFFFFFFu || lo != 0xFFFFFFFFu) {
             const int best = __builtin_amdgcn_readfirstlane((int)lo);
-            rel = fmul(frame_inverse(fk.f[7]), object_frame(objs + 8 * best));
+            rel = fmul(frame_inverse(pick(fk, 7)), object_frame(objs + 8 * best));
             held = best;
         }
     } else if (!grasp && held >= 0) {
-        const Frame F = fmul(fk.f[7], rel);
+        const Frame F = fmul(pick(fk, 7), rel);
         place_object(rp, sb, gm, env, held, F, objs, episode, t, lane);
         held = -1;
         moved = true;
@@ -946,7 +1012,7 @@ __global__ __launch_bounds__(256) void k_robot_step_manip(RobotParams rp, SimBuf
         held = -1;
         const float *o0 = sb.objects + (size_t)env * O * 8;
         for (int i = lane; i < O * 8; i += 64) objs[i] = o0[i];
-        forward_kinematics(rp, st, fk);
+        wave_kinematics<64>(rp, st, lane, fk);
         moved = true;
     }
     if (moved) {
@@ -964,7 +1030,7 @@ __global__ __launch_bounds__(256) void k_robot_step_manip(RobotParams rp, SimBuf
 #pragma unroll
         for (int k = 0; k < 12; ++k) sb.rel[(size_t)env * 12 + k] = rel.m[k];
         float cam[12];
-        write_camera(rp, fk.f[0], cam);
+        write_camera(rp, pick(fk, 0), cam);
 #pragma unroll
         for (int k = 0; k < 12; ++k) sb.camera[(size_t)env * 12 + k] = cam[k];
         if (out.state)
@@ -992,7 +1058,7 @@ __global__ __launch_bounds__(256) void k_robot_step_manip(RobotParams rp, SimBuf
         }
     }
     if (lane < O) {
-        const Frame Fo = lane == held ? fmul(fk.f[7], rel) : object_frame(objs + 8 * lane);
+        const Frame Fo = lane == held ? fmul(pick(fk, 7), rel) : object_frame(objs + 8 * lane);
         float *dst = sb.obj_frames + ((size_t)env * O + lane) * 12;
 #pragma unroll
         for (int k = 0; k < 12; ++k) dst[k] = Fo.m[k];
@@ -1015,13 +1081,14 @@ __global__ __launch_bounds__(256) void k_object_frames(RobotParams rp, SimBuffer
 #pragma unroll
     for (int k = 0; k < 10; ++k) st[k] = sb.state[(size_t)env * 10 + k];
     const int held = sb.held_obj[env];
-    Fk fk;
-    forward_kinematics(rp, st, fk);
+    __shared__ float4 fk_lds[4][kFkRows];
+    float4 *fk = fk_lds[(int)threadIdx.x / 64];
+    wave_kinematics<64>(rp, st, lane, fk);
     Frame rel;
 #pragma unroll
     for (int k = 0; k < 12; ++k) rel.m[k] = sb.rel[(size_t)env * 12 + k];
     if (lane < O) {
-        const Frame Fo = lane == held ? fmul(fk.f[7], rel)
+        const Frame Fo = lane == held ? fmul(pick(fk, 7), rel)
                                       : object_frame(sb.obj_dyn + ((size_t)env * O + lane) * 8);
         float *dst = sb.obj_frames + ((size_t)env * O + lane) * 12;
 #pragma unroll
