@@ -299,8 +299,7 @@ int gal_step(gal_batch *b, const float *actions_dev, const gal_outputs *out, voi
  *  prologue   clusters drawn before the first occlusion test (>= 0)
  *  persistent 1 = one persistent raster kernel whose workgroups drain the
  *             (env, region) work queue, longest items first; 0 = one
- *             workgroup per item (more items than are resident at once are
- *             started in the order of their times in the previous step)
+ *             workgroup per item
  *  robot_lanes lanes per environment in the robot-step kernel: 64 (one env
  *             per wave) or 32 (two envs per wave)
  *  graph      1 = gal_step replays the whole step as a captured hipGraph
@@ -311,10 +310,11 @@ int gal_step(gal_batch *b, const float *actions_dev, const gal_outputs *out, voi
  *             items per region instead of one) so that the last items of a
  *             launch are short; envs whose region side is not a multiple of
  *             16 are not split
- *  order      with the persistent queue: 1 = each step drains the items in
- *             the order of their times in the previous step, longest first
- *             (measured on the device; up to 32768 items, the static order
- *             beyond), 0 = the static order by cluster count
+ *  order      1 = each step takes the items in the order of their times in
+ *             the previous step, longest first (measured on the device; up
+ *             to 32768 items, the static order beyond; with one workgroup
+ *             per item only where more items than are resident at once), 0
+ *             = the static order by cluster count
  *  objgrid    1 = a sphere's resting-object candidates come from four offset
  *             regular grids of 0.5 m cells (Appendix G: any sphere of
  *             radius <= 12.5 cm lies wholly inside a cell of one of them;
@@ -333,7 +333,7 @@ int gal_step(gal_batch *b, const float *actions_dev, const gal_outputs *out, voi
  *             the contacts are the same either way.  Not with GAL_MANIP
  * A new batch starts with block 512, region 128 (or the resolution, if
  * smaller), lane_max 8, small_max 1024, occlusion 1 with refresh 1 and
- * prologue 128, persistent 0, robot_lanes 64, graph 0, split 0, order 0,
+ * prologue 128, persistent 0, robot_lanes 64, graph 0, split 0, order 1,
  * objgrid 1 with 16 or more objects per env (else 0), bin 0, layer_cache 0.
  */
 typedef struct gal_tuning {
@@ -361,6 +361,14 @@ typedef struct gal_tuning {
 int gal_get_tuning(const gal_batch *b, gal_tuning *t);
 int gal_set_tuning(gal_batch *b, const gal_tuning *t);
 
+/* How gal_step launches the raster with the present launch configuration
+ * (Section 3.1 batching extension), depth alone or (color 1) with the rgb
+ * output: the work items, the workgroups resident at once, the threads per
+ * workgroup, and whether the items follow their last times.  Any pointer may
+ * be NULL.  GAL_EINVAL for color 1 on a batch without GAL_COLOR. */
+int gal_launch_info(const gal_batch *b, int32_t color, int32_t *items, int32_t *resident, int32_t *block,
+                    int32_t *by_time);
+
 /*
  * Autotuner (this build's extension of Section 3.1 "Batching": the paper
  * fixes one batch size per GPU; here the split of the batch's work into
@@ -371,7 +379,7 @@ int gal_set_tuning(gal_batch *b, const gal_tuning *t);
  * outputs (`steps` timed steps each, HIP events); then, on the fastest and on
  * it with the other launch mode, `split` at 0, 1/16, 1/8, 1/4 and 1/2 of the
  * workgroups resident at once, each with an occlusion prologue of 128 and 256
- * clusters and, with the queue, both item orders (3 x `steps` each, two
+ * clusters and both item orders (3 x `steps` each, two
  * interleaved rounds); last, the robot step's 32 or 64 lanes per env on the
  * winner (3 x `steps` each, three interleaved rounds).  It
  * checks that every candidate produces the same depth bits from the same

@@ -236,7 +236,6 @@ struct gal_batch {
     int64_t n_clusters = 0, n_cverts = 0, n_tris = 0;
     unsigned long long *d_stats = nullptr;  // raster work counters (allocated on demand)
     std::vector<int64_t> cl_count_host;    // clusters per env
-    int64_t clusters = 0;                  // of all envs
     int32_t work_cap = 0;
     uint32_t *d_queue = nullptr;            // persistent raster work-queue counter
     // surrogate pre-filter
@@ -589,7 +588,7 @@ int gal_autotune(gal_batch *b, const float *actions_dev, const gal_outputs *out,
                                 t.robot_lanes = rl;
                                 t.graph = 0;
                                 t.split = 0;
-                                t.order = 0;
+                                t.order = 1 - persist;
                                 t.bin = 0;
                                 cands.push_back(t);
                             }
@@ -619,7 +618,7 @@ int gal_autotune(gal_batch *b, const float *actions_dev, const gal_outputs *out,
                         t.robot_lanes = 64;
                         t.graph = 0;
                         t.split = 0;
-                        t.order = 0;
+                        t.order = 1 - persist;
                         t.bin = 1;
                         cands.push_back(t);
                     }
@@ -689,7 +688,6 @@ int gal_autotune(gal_batch *b, const float *actions_dev, const gal_outputs *out,
                         if (!w.occlusion && pro != w.prologue) continue;
                         gal_tuning t = w;
                         if (flip) t.persistent = 1 - w.persistent;
-                        if (ord && !t.persistent) continue;
                         t.split = div ? std::min(b->N, std::max(1, slots / div)) : 0;
                         if (w.occlusion) t.prologue = pro;
                         t.order = ord;
@@ -1143,7 +1141,6 @@ int gal_create_batch(const gal_config *cfg, const gal_robot *robot, const gal_sc
         b->n_clusters = (int64_t)cl_off[N];
         b->cl_count_host.resize(N);
         for (int e = 0; e < N; ++e) b->cl_count_host[e] = (int64_t)(cl_off[e + 1] - cl_off[e]);
-        b->clusters = (int64_t)cl_off[N];
         b->n_cverts = (int64_t)nv_tot;
         b->n_tris = (int64_t)nt_tot;
         if (cfg->flags & GAL_COLOR) {
@@ -1191,7 +1188,7 @@ int gal_create_batch(const gal_config *cfg, const gal_robot *robot, const gal_sc
         b->rast.refresh = 1;
         b->rast.occlusion = 1;
         b->rast.prologue = 128;
-        b->rast.order = 0;
+        b->rast.order = 1;
         b->rast.stats = nullptr;
         if ((rc = b->mem.alloc(&b->d_res, (size_t)N)) || (rc = b->mem.alloc(&b->d_depth_off, (size_t)N + 1)))
             return cleanup(rc);
@@ -1289,6 +1286,40 @@ gal::SurInferArgs batch_features(const gal_batch *b, const float *actions_dev)
     return a;
 }
 
+// How the raster is launched with the present tuning: its parameters (threads per
+// workgroup, whether the items follow their last times) and the workgroups
+// resident at once.
+struct RasterLaunch {
+    gal::RasterParams rast;
+    int slots;
+};
+
+RasterLaunch raster_launch(const gal_batch *b, bool color)
+{
+    RasterLaunch l{b->rast, b->resident[color ? 1 : 0]};
+    // 1024 threads for 512, one workgroup per CU for two: where the z-buffer
+    // (with colour) leaves LDS for no second one, and up to two items per CU, all
+    // in flight at once either way but then sharing their CU unevenly; there only
+    // with clusters enough for the waves.  512 and 1024 threads: 512 with colour
+    // 229 and 174 us; 512 apartments 156 and 134, 600 of them 148 and 148, 768 of
+    // them 153 and 181; 256 uneven scenes (512 items) 183 and 146; 128 one-room
+    // scenes (512 items, 10 clusters each) 42 and 51.
+    const bool many = b->n_clusters >= 64 * (int64_t)b->N;
+    if (l.rast.block == 512 && !l.rast.bin &&
+        (l.slots <= b->num_cus || (many && b->num_work <= 2 * b->num_cus))) {
+        l.rast.block = 1024;
+        l.slots = b->num_cus;
+    }
+    // One workgroup per item starts the items by their last times wherever they
+    // are not all resident at once: cameras move little between steps, and the
+    // cluster count that the static order goes by says little about an item's
+    // time (correlation 0.2), so the last workgroups to start are often long ones
+    // (1024 apartments: the launch takes 226 us in the static order, the step 247
+    // us, and 193 in this one)
+    if ((!l.rast.persistent && b->num_work <= l.slots) || b->num_work > gal::kOrderCap) l.rast.order = 0;
+    return l;
+}
+
 // Enqueue one step (robot kernel, then raster) on stream s.
 int enqueue_step(gal_batch *b, const float *actions_dev, const gal_outputs *out, hipStream_t s,
                  hipEvent_t *ev)
@@ -1317,36 +1348,16 @@ int enqueue_step(gal_batch *b, const float *actions_dev, const gal_outputs *out,
         sb.sur_stats = b->d_sur_stats;
     }
     if (ev) HIP_TRY(hipEventRecord(ev[1], s));
-    // the raster items' order (from the previous step's item times) is computed
-    // by an extra workgroup of the robot launch.  One workgroup per item starts
-    // them in that order wherever they are not all resident at once: cameras
-    // move little between steps, and the cluster count that the static order
-    // goes by says little about an item's time (correlation 0.2), so the last
-    // workgroups to start are often long ones (1024 apartments: the launch takes
-    // 226 us in the static order, the step 247 us, and 193 in this one)
-    gal::RasterParams rast = b->rast;
-    int slots = b->resident[out->rgb ? 1 : 0];
-    // 1024 threads for 512, one workgroup per CU for two: where the z-buffer
-    // (with colour) leaves LDS for no second one, and up to two items per CU, all
-    // in flight at once either way but then sharing their CU unevenly; there only
-    // with clusters enough for the waves.  512 and 1024 threads: 512 with colour
-    // 229 and 174 us; 512 apartments 156 and 134, 600 of them 148 and 148, 768 of
-    // them 153 and 181; 256 uneven scenes (512 items) 183 and 146; 128 one-room
-    // scenes (512 items, 10 clusters each) 42 and 51.
-    const bool many = b->clusters >= 64 * (int64_t)b->N;
-    if (rast.block == 512 && !rast.bin && (slots <= b->num_cus || (many && b->num_work <= 2 * b->num_cus))) {
-        rast.block = 1024;
-        slots = b->num_cus;
-    }
-    const bool by_time = rast.persistent ? rast.order != 0 : b->num_work > slots;
-    const bool order_items = out->depth && by_time && b->num_work <= gal::kOrderCap;
-    rast.order = order_items ? 1 : 0;
+    // the raster items' order (from the previous step's item times) is computed by
+    // an extra workgroup of the robot launch
+    const RasterLaunch rl = raster_launch(b, out->rgb != nullptr);
+    const bool order_items = out->depth && rl.rast.order;
     const gal::ItemOrder ord{b->d_item_cost, order_items ? b->num_work : 0, b->d_item_order};
     HIP_TRY(gal::launch_robot_step(b->rp, sb, actions_dev, so, b->d_queue, b->robot_lanes, ord, s));
     if (ev) HIP_TRY(hipEventRecord(ev[2], s));
     if (out->depth)
-        HIP_TRY(gal::launch_raster(b->mesh, rast, b->sb.camera, b->d_res, b->d_depth_off, b->d_work,
-                                   b->num_work, b->item_region, b->d_queue, slots, out->depth,
+        HIP_TRY(gal::launch_raster(b->mesh, rl.rast, b->sb.camera, b->d_res, b->d_depth_off, b->d_work,
+                                   b->num_work, b->item_region, b->d_queue, rl.slots, out->depth,
                                    out->rgb, s));
     if (ev) HIP_TRY(hipEventRecord(ev[3], s));
     return GAL_OK;
@@ -1410,6 +1421,19 @@ int gal_step(gal_batch *b, const float *actions_dev, const gal_outputs *out, voi
     }
     if (b->use_graph) return graph_step(b, actions_dev, out, s);
     return enqueue_step(b, actions_dev, out, s, nullptr);
+}
+
+int gal_launch_info(const gal_batch *b, int32_t color, int32_t *items, int32_t *resident, int32_t *block,
+                    int32_t *by_time)
+{
+    if (!b) return fail(GAL_EINVAL, "null batch");
+    if (color && !(b->flags & GAL_COLOR)) return fail(GAL_EINVAL, "the batch was created without GAL_COLOR");
+    const RasterLaunch l = raster_launch(b, color != 0);
+    if (items) *items = b->num_work;
+    if (resident) *resident = l.slots;
+    if (block) *block = l.rast.block;
+    if (by_time) *by_time = l.rast.order;
+    return GAL_OK;
 }
 
 int gal_profile_enable(gal_batch *b, int on)

@@ -107,6 +107,7 @@ def load_library():
         L.gal_autotune.argtypes = [C.c_void_p, C.c_void_p, C.POINTER(GalOutputs), C.c_void_p,
                                    C.c_int32, C.POINTER(GalTuning), C.POINTER(C.c_double)]
         L.gal_get_tuning.argtypes = [C.c_void_p, C.POINTER(GalTuning)]
+        L.gal_launch_info.argtypes = [C.c_void_p, C.c_int32] + [C.POINTER(C.c_int32)] * 4
         L.gal_mlp_num_params.argtypes = [_i64p]
         L.gal_mlp_create.argtypes = [C.c_int32, C.c_uint64, C.POINTER(C.c_void_p)]
         L.gal_mlp_set_weights.argtypes = [C.c_void_p, _fp, C.c_size_t]
@@ -447,6 +448,12 @@ class Batch:
         cur.update(kw)
         t = GalTuning(**cur)
         _check(load_library().gal_set_tuning(self._h, C.byref(t)))
+
+    def launch_info(self, color: bool = False) -> dict:
+        """How step() launches the raster (see gal_launch_info in include/gal.h)."""
+        v = [C.c_int32() for _ in range(4)]
+        _check(load_library().gal_launch_info(self._h, 1 if color else 0, *[C.byref(x) for x in v]))
+        return dict(zip(("items", "resident", "block", "by_time"), (x.value for x in v)))
 
     COUNTERS = ("clusters_tested", "clusters_in_frustum", "clusters_occluded", "clusters_drawn",
                 "tris_valid", "tris_clipped", "tris_setup", "cand_pixels")

@@ -1,0 +1,70 @@
+"""One workgroup per item, more items than are resident at once: the setting
+`order` chooses whether the items are started by their times in the step before
+(1, a new batch's) or in the static order (0), which must change no bit: with
+graph replay, colour, split items and after resets, each case with a launch that
+is asserted to follow the times."""
+import numpy as np
+import pytest
+
+from paper_2306_07552_amd import scenegen as sg
+
+pytestmark = pytest.mark.gpu
+
+
+def make(n, color):
+    from paper_2306_07552_amd import gal
+    cfg = sg.scaled_config(0, n)
+    scenes = sg.make_scene_set(cfg)
+    return cfg, gal.Batch(sg.make_robot_for(cfg), scenes, sg.config_constants(cfg), color=color)
+
+
+@pytest.mark.parametrize("n,color,tuning", [
+    (1300, False, {}),
+    (1300, True, {"graph": 1}),
+    (1000, False, {"region": 64, "split": 400, "graph": 1}),   # one item per env, four of a split one
+    (700, True, {"region": 32, "block": 256}),                 # four items per env
+])
+def test_items_started_by_their_times(n, color, tuning):
+    import torch
+    print("case: item starts", n, color, tuning, flush=True)
+    cfg, b = make(n, color)
+    _, ref = make(n, color)
+    b.set_tuning(**tuning)
+    ref.set_tuning(**dict(tuning, graph=0, order=0))
+    info, plain = b.launch_info(color), ref.launch_info(color)
+    assert info["items"] == plain["items"] > info["resident"] > 0, info
+    assert info["by_time"] == 1 and plain["by_time"] == 0
+    out, want = b.alloc_outputs(), ref.alloc_outputs()
+    acts = torch.empty((n, 9), device="cuda")
+    mask = torch.from_numpy((np.arange(n) % 3 == 0).astype(np.uint8)).cuda()
+    for k in range(6):
+        if k == 2:
+            b.reset(mask)
+            ref.reset(mask)
+        if k == 4:
+            b.reset()
+            ref.reset()
+        acts.copy_(torch.from_numpy(sg.actions(cfg, k, num_envs=n)))
+        b.step(acts, out)
+        ref.step(acts, want)
+        torch.cuda.synchronize()
+        for name in want:
+            assert torch.equal(out[name], want[name]), (k, name)
+
+
+def test_order_setting():
+    """What each setting launches: the times are followed by the queue at any
+    number of items, by one workgroup per item above the resident ones."""
+    import torch  # noqa: F401
+    print("case: order setting", flush=True)
+    _, b = make(1300, False)
+    _, few = make(40, False)
+    for persistent in (0, 1):
+        for order in (0, 1):
+            for batch, more in ((b, True), (few, False)):
+                batch.set_tuning(persistent=persistent, order=order)
+                info = batch.launch_info()
+                assert (info["items"] > info["resident"]) == more
+                assert info["by_time"] == (order if more or persistent else 0)
+    with pytest.raises(RuntimeError):
+        b.launch_info(color=True)
