@@ -1313,9 +1313,11 @@ RasterLaunch raster_launch(const gal_batch *b, bool color)
     // One workgroup per item starts the items by their last times wherever they
     // are not all resident at once: cameras move little between steps, and the
     // cluster count that the static order goes by says little about an item's
-    // time (correlation 0.2), so the last workgroups to start are often long ones
-    // (1024 apartments: the launch takes 226 us in the static order, the step 247
-    // us, and 193 in this one)
+    // time (correlation 0.2), so the last workgroups to start are often long ones.
+    // The step in the static order and in this one, us: 600 rooms 62 and 54, 4096
+    // of them 230 and 216, 32768 of them 1683 and 1645; apartments at 256 pixels,
+    // 1024 items 238 and 172, 4096 items 657 and 466; 2048 envs with manipulation
+    // 452 and 380.
     if ((!l.rast.persistent && b->num_work <= l.slots) || b->num_work > gal::kOrderCap) l.rast.order = 0;
     return l;
 }

@@ -1,5 +1,5 @@
 // Raster queue order computed inside the robot-step launch (not part of the
-// ABI): one extra workgroup of the robot kernel sorts the work items by the
+// ABI): one extra workgroup of the robot kernel, its first, sorts the work items by the
 // previous step's measured times while the other workgroups step the envs,
 // so the order costs no launch of its own on the step's critical path.
 #pragma once

@@ -322,27 +322,55 @@ __device__ __forceinline__ void load_slots(const RobotParams &rp, const SimBuffe
     }
 }
 
-// Queue order of the raster work items by descending cost, to within 1/256
-// of the largest: a counting sort of the costs quantised to 256 buckets by
-// one 256-thread workgroup (three passes over the costs; the order inside a
-// bucket is whatever the LDS atomics give, and the order of the items changes
-// no output).
-__device__ void order_items_block(const ItemOrder &ord)
+// Order of the raster work items by descending cost, to within 1/256 of the
+// largest: a counting sort of the costs quantised to 256 buckets by one
+// 256-thread workgroup, in three passes over the costs (maximum, counts, places;
+// the order inside a bucket is whatever the LDS atomics give, and the order of
+// the items changes no output).  The raster waits for it, so what it costs beyond
+// the robot workgroups beside it is lost.  Latency and instructions bound it:
+// the costs come 16 per thread at a time, all in flight, and up to 4096 of them
+// stay in registers for all passes; a cost's bucket is one multiplication, and the
+// workgroup is the launch's first, so that it starts with the robot's.  The robot
+// stage of 4096, 8192 and 32768 rooms with the sort 15, 26 and 77 us, as without
+// it (with a 64-bit division per cost and pass, 14 ns an item: 61 and 120 us at
+// 4096 and 8192).
+__device__ __forceinline__ void order_items_block(const ItemOrder &ord)
 {
-    constexpr int kBuckets = 256;
-    __shared__ uint32_t cmax;
+    constexpr int kBuckets = 256, kThreads = 256, kPer = 16, kChunk = kThreads * kPer;
+    __shared__ uint32_t wave_max[kThreads / 64];
     __shared__ uint32_t count[kBuckets];
     const int t = (int)threadIdx.x, n = ord.n;
-    if (t == 0) cmax = 1u;
-    count[t] = 0u;
-    __syncthreads();
-    for (int i = t; i < n; i += 256) atomicMax(&cmax, ord.cost[i]);
-    __syncthreads();
-    const uint64_t m = cmax;
-    auto bucket = [&](uint32_t c) {   // longest first: bucket 0 holds the largest costs
-        return (uint32_t)(kBuckets - 1) - (uint32_t)(((uint64_t)c * (kBuckets - 1)) / m);
+    uint32_t c[kPer];
+    const auto load = [&](int base) {
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const int i = base + k * kThreads + t;
+            c[k] = ord.cost[min(i, n - 1)];
+        }
     };
-    for (int i = t; i < n; i += 256) atomicAdd(&count[bucket(ord.cost[i])], 1u);
+    count[t] = 0u;
+    uint32_t m = 1u;
+    for (int base = 0; base < n; base += kChunk) {
+        load(base);
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) m = max(m, c[k]);
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, d, 64));
+    if ((t & 63) == 0) wave_max[t >> 6] = m;
+    __syncthreads();
+    m = max(max(wave_max[0], wave_max[1]), max(wave_max[2], wave_max[3]));
+    const float scale = (float)kBuckets / (float)m;
+    // longest first: bucket 0 holds the largest costs
+    const auto bucket = [&](uint32_t v) {
+        return (uint32_t)max(kBuckets - 1 - (int)((float)v * scale), 0);
+    };
+    for (int base = 0; base < n; base += kChunk) {
+        if (n > kChunk) load(base);
+#pragma unroll
+        for (int k = 0; k < kPer; ++k)
+            if (base + k * kThreads + t < n) atomicAdd(&count[bucket(c[k])], 1u);
+    }
     __syncthreads();
     if (t < 64) {   // exclusive prefix over the buckets, 4 per lane
         const uint32_t a = count[4 * t], b = count[4 * t + 1], d = count[4 * t + 2], e = count[4 * t + 3];
@@ -360,7 +388,18 @@ __device__ void order_items_block(const ItemOrder &ord)
         count[4 * t + 3] = ex + a + b + d;
     }
     __syncthreads();
-    for (int i = t; i < n; i += 256) ord.order[atomicAdd(&count[bucket(ord.cost[i])], 1u)] = (uint32_t)i;
+    for (int base = 0; base < n; base += kChunk) {
+        if (n > kChunk) load(base);
+        uint32_t at[kPer];
+#pragma unroll
+        for (int k = 0; k < kPer; ++k)
+            if (base + k * kThreads + t < n) at[k] = atomicAdd(&count[bucket(c[k])], 1u);
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const int i = base + k * kThreads + t;
+            if (i < n) ord.order[at[k]] = (uint32_t)i;
+        }
+    }
 }
 
 // kLanes lanes per environment: 64 (one env per wave, spheres lane + 64k) or
@@ -372,19 +411,20 @@ __global__ __launch_bounds__(256) void k_robot_step(RobotParams rp, SimBuffers s
                                                     StepOutputs out, uint32_t *queue_reset,
                                                     ItemOrder ord)
 {
-    // the launch's extra last workgroup orders the raster queue
-    if (ord.n > 0 && blockIdx.x == gridDim.x - 1) {
+    // the launch's extra first workgroup orders the raster items
+    if (ord.n > 0 && blockIdx.x == 0) {
         order_items_block(ord);
         return;
     }
+    const int block = (int)blockIdx.x - (ord.n > 0 ? 1 : 0);
     // the raster work queue of this step starts empty (a kernel store rather
     // than a memset, so the step can be captured as a graph)
-    if (queue_reset && blockIdx.x == 0 && threadIdx.x == 0) *queue_reset = 0u;
+    if (queue_reset && block == 0 && threadIdx.x == 0) *queue_reset = 0u;
     constexpr int kEnvsPerBlock = 256 / kLanes;
     const int lane = threadIdx.x & 63;
     const int sub = (int)threadIdx.x % kLanes;
     const int half = kLanes == 32 ? (lane >> 5) : 0;
-    int env = (int)blockIdx.x * kEnvsPerBlock + (int)threadIdx.x / kLanes;
+    int env = block * kEnvsPerBlock + (int)threadIdx.x / kLanes;
     if (kLanes == 64) env = __builtin_amdgcn_readfirstlane(env);
     // with two envs per wave, a half-wave past the end still joins the ballots
     const bool active = env < sb.num_envs;
@@ -412,7 +452,7 @@ __global__ __launch_bounds__(256) void k_robot_step(RobotParams rp, SimBuffers s
     // the chain would wait on a load of its own.
     __shared__ float4 obj_lds[kEnvsPerBlock * kMaxObjects * 2];
     __shared__ float4 fk_lds[kEnvsPerBlock][kFkRows];
-    const int env0 = (int)blockIdx.x * kEnvsPerBlock;
+    const int env0 = block * kEnvsPerBlock;
     {
         const int ne = min(kEnvsPerBlock, sb.num_envs - env0);
         const int n4 = ne * rp.num_objects * 2;
@@ -889,13 +929,14 @@ __global__ __launch_bounds__(256) void k_robot_step_manip(RobotParams rp, SimBuf
                                                           StepOutputs out, uint32_t *queue_reset,
                                                           ItemOrder ord)
 {
-    if (ord.n > 0 && blockIdx.x == gridDim.x - 1) {
+    if (ord.n > 0 && blockIdx.x == 0) {
         order_items_block(ord);
         return;
     }
-    if (queue_reset && blockIdx.x == 0 && threadIdx.x == 0) *queue_reset = 0u;
+    const int block = (int)blockIdx.x - (ord.n > 0 ? 1 : 0);
+    if (queue_reset && block == 0 && threadIdx.x == 0) *queue_reset = 0u;
     const int lane = threadIdx.x & 63;
-    const int env = __builtin_amdgcn_readfirstlane((int)blockIdx.x * 4 + (int)threadIdx.x / 64);
+    const int env = __builtin_amdgcn_readfirstlane(block * 4 + (int)threadIdx.x / 64);
     if (env >= sb.num_envs) return;
     const int O = rp.num_objects;
     float st[10];

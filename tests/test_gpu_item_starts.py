@@ -68,3 +68,30 @@ def test_order_setting():
                 assert info["by_time"] == (order if more or persistent else 0)
     with pytest.raises(RuntimeError):
         b.launch_info(color=True)
+
+
+@pytest.mark.parametrize("n,lanes", [(4096, 64), (8192, 32)])
+def test_ordering_is_hidden_beside_the_robot_step(n, lanes):
+    """The sort of the items' times runs in one workgroup beside the robot step's
+    and the raster waits for it: at thousands of items it may not lengthen the
+    robot stage by more than 15 us (about 0.5 of its 31 and 62 us; a sort of 14 ns
+    an item took 46 and 92 us more).  The shortest of 40 steps of each, in turn."""
+    import torch
+    print("case: ordering hidden", n, lanes, flush=True)
+    cfg, b = make(n, False)
+    out = b.alloc_outputs()
+    acts = torch.from_numpy(sg.actions(cfg, 0, num_envs=n)).cuda()
+    best = [1e9, 1e9]
+    for k in range(43):
+        for order in (0, 1):
+            b.set_tuning(order=order, robot_lanes=lanes)
+            assert b.launch_info()["by_time"] == order
+            b.profile(True)
+            b.step(acts, out)
+            torch.cuda.synchronize()
+            b.profile(False)
+            _, robot, _, _ = b.profile_read_stages()
+            if k >= 3:
+                best[order] = min(best[order], robot)
+    print("robot stage, ms: static %.4f, by time %.4f" % tuple(best), flush=True)
+    assert best[1] - best[0] < 0.015
