@@ -369,6 +369,12 @@ int gal_set_tuning(gal_batch *b, const gal_tuning *t);
 int gal_launch_info(const gal_batch *b, int32_t color, int32_t *items, int32_t *resident, int32_t *block,
                     int32_t *by_time);
 
+/* The divisions of the Section 3.1 renderer's vertex projection alone (for
+ * verification): quotient[i] = x[i] / z[i] and recip[i] = 1 / z[i], correctly
+ * rounded (for |x| < 2^-60 to within what the half image width absorbs). */
+int gal_project_test(const float *x_dev, const float *z_dev, int64_t n, float *quotient_dev, float *recip_dev,
+                     void *stream);
+
 /*
  * Autotuner (this build's extension of Section 3.1 "Batching": the paper
  * fixes one batch size per GPU; here the split of the batch's work into

@@ -1425,6 +1425,14 @@ int gal_step(gal_batch *b, const float *actions_dev, const gal_outputs *out, voi
     return enqueue_step(b, actions_dev, out, s, nullptr);
 }
 
+int gal_project_test(const float *x_dev, const float *z_dev, int64_t n, float *quotient_dev, float *recip_dev,
+                     void *stream)
+{
+    if (!x_dev || !z_dev || !quotient_dev || !recip_dev || n < 0) return fail(GAL_EINVAL, "bad arguments");
+    HIP_TRY(gal::launch_divide(x_dev, z_dev, n, quotient_dev, recip_dev, (hipStream_t)stream));
+    return GAL_OK;
+}
+
 int gal_launch_info(const gal_batch *b, int32_t color, int32_t *items, int32_t *resident, int32_t *block,
                     int32_t *by_time)
 {

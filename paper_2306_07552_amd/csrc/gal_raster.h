@@ -69,6 +69,8 @@ struct RasterParams {
     const uint32_t *item_order; // [work] queue or launch position -> work item
 };
 
+// q = x / z and inv = 1 / z as the vertex projection computes them.
+hipError_t launch_divide(const float *x, const float *z, int64_t n, float *q, float *inv, hipStream_t s);
 hipError_t raster_prepare();   // raises the dynamic-LDS limit of the raster kernels
 // Workgroups of the persistent raster kernel that fit on the device at once.
 int raster_persistent_grid(const RasterParams &rp, int max_region, bool color);

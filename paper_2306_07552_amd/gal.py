@@ -108,6 +108,7 @@ def load_library():
                                    C.c_int32, C.POINTER(GalTuning), C.POINTER(C.c_double)]
         L.gal_get_tuning.argtypes = [C.c_void_p, C.POINTER(GalTuning)]
         L.gal_launch_info.argtypes = [C.c_void_p, C.c_int32] + [C.POINTER(C.c_int32)] * 4
+        L.gal_project_test.argtypes = [C.c_void_p, C.c_void_p, C.c_int64] + [C.c_void_p] * 3
         L.gal_mlp_num_params.argtypes = [_i64p]
         L.gal_mlp_create.argtypes = [C.c_int32, C.c_uint64, C.POINTER(C.c_void_p)]
         L.gal_mlp_set_weights.argtypes = [C.c_void_p, _fp, C.c_size_t]
@@ -565,6 +566,11 @@ class Mlp:
 def gemm_test(variant, a, b, M, N, K, lda, ldb, c, ldc, stream=None):
     _check(load_library().gal_mlp_gemm_test(variant, a.data_ptr(), b.data_ptr(), M, N, K, lda, ldb,
                                             c.data_ptr(), ldc, _stream_handle(stream)))
+
+
+def project_test(x, z, q, inv, stream=None):
+    _check(load_library().gal_project_test(x.data_ptr(), z.data_ptr(), x.numel(), q.data_ptr(), inv.data_ptr(),
+                                           _stream_handle(stream)))
 
 
 class Policy:
