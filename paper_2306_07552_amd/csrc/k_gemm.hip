@@ -65,6 +65,9 @@ __device__ __forceinline__ uint32_t lds_addr(const void *p)
     return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void *)p;
 }
 
+// what a k-strided operand's rows past the last k are read from
+__device__ const quad kZeros[1] = {};
+
 // One operand's tile in LDS: R rows (m or n) x 64 k of BF16.
 //  k-contiguous: R rows of 128 bytes, 8 slots of 8 k, the slot XORed with a key
 //    of the row: its low 3 bits (A), or for B, whose fragments take rows 0..3,
@@ -97,13 +100,20 @@ struct Tile {
             }
         }
     }
-    // request stage k0 .. k0 + 63 of p (k beyond klast repeats valid values)
+    // request stage k0 .. k0 + 63 of p; beyond klast: zeros (k-strided, where K may
+    // end anywhere), or valid values that no step takes (k-contiguous)
     __device__ __forceinline__ void fetch(const uint16_t *p, int ld, int k0, int klast, uint32_t lds, int wave) const
     {
+        const bool tail = k0 + kStageK - 1 > klast;
 #pragma unroll
         for (int i = 0; i < kDma; ++i) {
-            const uint16_t *src = kStrided ? p + (size_t)min(k0 + krow[i], klast) * ld + off[i]
-                                           : p + (size_t)off[i] * ld + min(k0 + krow[i], klast - 7);
+            const uint16_t *src;
+            if (kStrided) {
+                src = p + (size_t)(k0 + krow[i]) * ld + off[i];
+                if (tail && k0 + krow[i] > klast) src = reinterpret_cast<const uint16_t *>(kZeros);
+            } else {
+                src = p + (size_t)off[i] * ld + min(k0 + krow[i], klast - 7);
+            }
             dma16(src, lds + (wave * kDma + i) * 1024);
         }
     }
@@ -191,12 +201,6 @@ __device__ __forceinline__ void tile_products(const uint16_t *a, int lda, int M,
         if (s + kAhead < nst) fetch(s + kAhead);
         unsigned char *sa = lds + buf * kStageBytes, *sb = sa + TA::kBytes;
         const int left = kend - (kbeg + s * kStageK);   // k of this stage
-        if (kSA && kSB && left < kStageK) {
-            // rows past the last k repeat it: zero them on one side
-            for (int i = threadIdx.x; i < (kStageK - left) * TM / 8; i += 256)
-                *reinterpret_cast<quad *>(sa + left * TM * 2 + i * 16) = quad{0u, 0u, 0u, 0u};
-            __syncthreads();
-        }
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
             if (ks == 1 && left <= 32) break;

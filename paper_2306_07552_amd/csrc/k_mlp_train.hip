@@ -184,8 +184,12 @@ __global__ __launch_bounds__(kThreads, 2) void k_mlp_mid(MlpMidArgs p)
             if (row0 + r < p.rows) *reinterpret_cast<bf16x8 *>(p.dp[3] + (size_t)(row0 + r) * D + c) = o;
         }
         if (tid < D) {
+            if (row0 + R <= p.rows) {
 #pragma unroll
-            for (int r = 0; r < R; ++r) head += dzs[r] * bf2f(H[3][r][tid]);
+                for (int r = 0; r < R; ++r) head += dzs[r] * bf2f(H[3][r][tid]);
+            } else {   // (rows past the last repeat it, and may be infinite)
+                for (int r = 0; row0 + r < p.rows; ++r) head += dzs[r] * bf2f(H[3][r][tid]);
+            }
         } else if (tid < D + 2) {
             const float *v = tid == D ? dzs : losses;
             for (int r = 0; r < R; ++r) head += v[r];
