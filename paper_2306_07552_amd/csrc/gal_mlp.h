@@ -76,8 +76,6 @@ hipError_t gemm_dw_group(const DwJob *jobs, int n, int rows, float *part, int64_
 // be null).
 hipError_t mlp_grad_sum(const float *part, int splits, int64_t i0, int64_t n, const float *hpart, int hslabs, float *g,
                         float *grads, float *loss, float *loss_out, hipStream_t s);
-// Column sums of a BF16 [rows][D] matrix.
-hipError_t mlp_colsum(const uint16_t *g, int rows, int D, float *out, hipStream_t s);
 hipError_t mlp_adam(float *w, float *m, float *v, const float *g, int64_t n, float lr, float b1,
                     float b2, float eps, int64_t t, uint16_t *wb, hipStream_t s);
 hipError_t mlp_to_bf16(const float *a, int64_t n, uint16_t *out, hipStream_t s);

@@ -210,22 +210,24 @@ int mlp_gradients_rows(gal_mlp *m, const uint16_t *x, const float *y, int rows, 
     a.part = m->head_part;
     int slabs = 0, splits = 0;
     MLP_TRY(mlp_mid(a, &slabs, s));
-    // the weight gradients (inputs that are not 16-byte aligned by the general
-    // GEMM, straight into m->g)
+    // the weight gradients.  The first layer's, where the inputs are not 16-byte
+    // aligned, comes from the general GEMM straight into m->g; its bias gradient then
+    // rides on a product with the next layer's input, which lands in the slabs'
+    // unused place of the first layer's weights
     const bool aligned = (uintptr_t)x % 16 == 0;
     DwJob jobs[4];
-    int n = 0;
-    for (int l = aligned ? 0 : 1; l < 4; ++l)
-        jobs[n++] = DwJob{m->dp[l], l == 0 ? x : m->h[l], kDims[l], m->off_w[l], m->off_b[l]};
+    for (int l = 0; l < 4; ++l)
+        jobs[l] = DwJob{m->dp[l], l == 0 ? x : m->h[l], kDims[l], m->off_w[l], m->off_b[l]};
     if (!aligned) {
+        jobs[0].x = m->h[1];
+        jobs[0].N = kMlpHidden;
         MLP_TRY(mlp_gemm(kGemmDw, m->dp[0], x, kMlpHidden, kMlpIn, rows, kMlpHidden, kMlpIn, nullptr, nullptr, 0,
                          m->g + m->off_w[0], nullptr, kMlpIn, s, m->dw_part, m->dw_part_floats));
-        MLP_TRY(mlp_colsum(m->dp[0], rows, kMlpHidden, m->g + m->off_b[0], s));
         if (grads)
-            MLP_TRY(hipMemcpyAsync(grads, m->g, sizeof(float) * m->off_w[1], hipMemcpyDeviceToDevice, s));
+            MLP_TRY(hipMemcpyAsync(grads, m->g, sizeof(float) * m->off_b[0], hipMemcpyDeviceToDevice, s));
     }
-    MLP_TRY(gemm_dw_group(jobs, n, rows, m->dw_part, m->off_w[4], m->dw_part_floats, &splits, s));
-    MLP_TRY(mlp_grad_sum(m->dw_part, splits, aligned ? 0 : m->off_w[1], m->off_w[4], m->head_part, slabs, m->g, grads,
+    MLP_TRY(gemm_dw_group(jobs, 4, rows, m->dw_part, m->off_w[4], m->dw_part_floats, &splits, s));
+    MLP_TRY(mlp_grad_sum(m->dw_part, splits, aligned ? 0 : m->off_b[0], m->off_w[4], m->head_part, slabs, m->g, grads,
                          m->loss, loss_out, s));
     return GAL_OK;
 }

@@ -159,18 +159,6 @@ __global__ __launch_bounds__(256) void k_gemm(const uint16_t *__restrict__ A, co
             }
 }
 
-// bias gradient: column sums of a BF16 [rows][D] matrix, 64 rows per block
-// (out zeroed by the caller)
-__global__ void k_colsum(const uint16_t *__restrict__ g, int rows, int D, float *__restrict__ out)
-{
-    const int j = threadIdx.x;
-    const int i0 = blockIdx.x * 64, i1 = min(rows, i0 + 64);
-    if (j >= D) return;
-    float acc = 0.f;
-    for (int i = i0; i < i1; ++i) acc += bf2f(g[(size_t)i * D + j]);
-    atomicAdd(&out[j], acc);
-}
-
 // Adam on the FP32 master parameters, then their BF16 copy (weights only)
 __global__ void k_adam(float *__restrict__ w, float *__restrict__ m, float *__restrict__ v,
                        const float *__restrict__ g, int64_t n, float lr, float b1, float b2,
@@ -293,16 +281,6 @@ hipError_t mlp_gemm_parts(const uint16_t *A, const uint16_t *B, int M, int N, in
     const dim3 grid((N + kBN - 1) / kBN, (M + kBM - 1) / kBM, splits);
     hipLaunchKernelGGL((k_gemm<false, true, kEpiF32>), grid, dim3(256), 0, s, A, B, M, N, K, lda, ldb, nullptr,
                        nullptr, 0, part, nullptr, N);
-    return hipGetLastError();
-}
-
-hipError_t mlp_colsum(const uint16_t *g, int rows, int D, float *out, hipStream_t s)
-{
-    if (D > 1024) return hipErrorInvalidValue;
-    hipError_t e = hipMemsetAsync(out, 0, sizeof(float) * D, s);
-    if (e != hipSuccess || rows <= 0) return e;
-    const int threads = ((D + 63) / 64) * 64;
-    hipLaunchKernelGGL(k_colsum, dim3((rows + 63) / 64), dim3(threads), 0, s, g, rows, D, out);
     return hipGetLastError();
 }
 
