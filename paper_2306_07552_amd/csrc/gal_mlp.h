@@ -20,12 +20,18 @@ constexpr int kFeatPatchBase = 64; // first patch feature
 enum { kEpiF32 = 0, kEpiBiasReluBf16 = 1, kEpiMaskBf16 = 2 };
 enum { kGemmFwd = 0, kGemmDx, kGemmDw, kGemmNtF32, kGemmNnF32, kGemmTnF32 };
 
+constexpr int kMaxDwSplits = 16;
 // C = op(A) op(B) on the matrix cores (variants above).  The weight-gradient
 // variant splits its reduction over the rows into the FP32 workspace ws
 // (ws_floats values; NULL = no split) and sums the splits in a fixed order.
-constexpr int kMaxDwSplits = 16;
-// Split-K partial products of A B^T (A [M][K], B [N][K], BF16): split z of
-// K (in 32-column steps) into part + z M N, FP32 [M][N]; no reduction.
+// Operands that gemm_tiles does not take go to a general kernel, but for kGemmDx
+// (hipErrorInvalidValue).
+hipError_t mlp_gemm(int variant, const uint16_t *A, const uint16_t *B, int M, int N, int K, int lda,
+                    int ldb, const float *bias, const uint16_t *mask, int ldm, float *Cf,
+                    uint16_t *Cb, int ldc, hipStream_t s, float *ws = nullptr, size_t ws_floats = 0);
+// Split-K partial products of A B^T (A [M][K], B [N][K], BF16, as gemm_tiles
+// takes them): split z of K (in 32-column steps) into part + z M N, FP32 [M][N];
+// no reduction.
 hipError_t mlp_gemm_parts(const uint16_t *A, const uint16_t *B, int M, int N, int K, int lda, int ldb, int splits,
                           float *part, hipStream_t s);
 // The tiled GEMM behind the variants (k_gemm.hip), for 16-byte aligned rows:
@@ -36,9 +42,6 @@ bool gemm_tiles_fit(bool strided_a, bool strided_b, const uint16_t *A, const uin
 hipError_t gemm_tiles(int variant, const uint16_t *A, const uint16_t *B, int M, int N, int K, int lda, int ldb,
                       const float *bias, const uint16_t *mask, int ldm, float *Cf, uint16_t *Cb, int ldc, int splits,
                       hipStream_t s);
-hipError_t mlp_gemm(int variant, const uint16_t *A, const uint16_t *B, int M, int N, int K, int lda,
-                    int ldb, const float *bias, const uint16_t *mask, int ldm, float *Cf,
-                    uint16_t *Cb, int ldc, hipStream_t s, float *ws = nullptr, size_t ws_floats = 0);
 // Training, between the first layer's output h1 (BF16 [rows][256], ReLU) and the
 // weight gradients: layers 2..4, the logit, the weighted logistic loss and the
 // pre-activation gradients of layers 1..4 (dp[0..3], BF16 [rows][256]); h2, h3

@@ -1,6 +1,7 @@
 // Host runtime of the collision-surrogate MLP (declared in include/gal.h):
 // parameters, training step (forward, logistic loss, backward, Adam) and
-// inference, all on the device with the MFMA kernels of k_mlp.hip.
+// inference, all on the device with the MFMA kernels of k_gemm.hip, k_mlp.hip,
+// k_mlp_train.hip and k_sur_infer.hip.
 #include "gal.h"
 #include "gal_mlp.h"
 

@@ -1,7 +1,7 @@
 // Host runtime of the policy network that consumes the depth stack (declared
-// in include/gal.h): parameters and batched inference, on the device with the
-// implicit-GEMM convolutions and heads of k_policy.hip and the fully connected
-// layer on the surrogate's MFMA GEMM.
+// in include/gal.h): parameters, batched inference and the PPO update, on the
+// device with the convolutions of k_policy_enc.hip and k_policy_bwd.hip, the fully
+// connected layer of k_gemm.hip and the heads of k_policy.hip.
 #include "gal.h"
 #include "gal_mlp.h"
 #include "gal_policy.h"

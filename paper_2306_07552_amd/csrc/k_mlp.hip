@@ -6,6 +6,9 @@
 // 1 logit.  Weights and activations are BF16 (round to nearest even after
 // bias + ReLU), accumulation FP32, biases and master weights FP32.
 //
+// Here: the general GEMM (rows that are not 16-byte aligned, sizes that are no
+// multiples of 8; the rest is k_gemm.hip's), the sum of its splits, and Adam.
+//
 // GEMM: C[M][N] = sum_k opA[m][k] * opB[k][n] with
 //   opA[m][k] = TA ? A[k*lda + m] : A[m*lda + k]
 //   opB[k][n] = TB ? B[n*ldb + k] : B[k*ldb + n]
@@ -42,7 +45,6 @@ template <bool TA, bool TB, int EPI>
 __global__ __launch_bounds__(256) void k_gemm(const uint16_t *__restrict__ A, const uint16_t *__restrict__ B,
                                               int M, int N, int K, int lda, int ldb,
                                               const float *__restrict__ bias,
-                                              const uint16_t *__restrict__ mask, int ldm,
                                               float *__restrict__ Cf, uint16_t *__restrict__ Cb,
                                               int ldc)
 {
@@ -147,14 +149,10 @@ __global__ __launch_bounds__(256) void k_gemm(const uint16_t *__restrict__ A, co
                 if (EPI == kEpiF32) {
                     if (bias) v += bias[n];
                     Cf[(size_t)m * ldc + n] = v;
-                } else if (EPI == kEpiBiasReluBf16) {
+                } else {   // kEpiBiasReluBf16
                     v += bias[n];
                     v = v > 0.f ? v : 0.f;
                     Cb[(size_t)m * ldc + n] = f2bf(v);
-                } else {   // kEpiMaskBf16: gradient through ReLU
-                    const uint16_t h = mask[(size_t)m * ldm + n];
-                    const bool on = (h & 0x8000u) == 0 && (h & 0x7FFFu) != 0;
-                    Cb[(size_t)m * ldc + n] = f2bf(on ? v : 0.f);
                 }
             }
 }
@@ -194,14 +192,14 @@ __global__ void k_sum_splits(const float *__restrict__ part, int splits, int64_t
 
 template <bool TA, bool TB, int EPI>
 hipError_t gemm(const uint16_t *A, const uint16_t *B, int M, int N, int K, int lda, int ldb,
-                const float *bias, const uint16_t *mask, int ldm, float *Cf, uint16_t *Cb, int ldc,
-                hipStream_t s, int splits = 1, float *part = nullptr)
+                const float *bias, float *Cf, uint16_t *Cb, int ldc, hipStream_t s, int splits = 1,
+                float *part = nullptr)
 {
     dim3 grid((N + kBN - 1) / kBN, (M + kBM - 1) / kBM, splits > 1 ? splits : 1);
     if (splits > 1) {
         // each split into its own [M][N] slab of part, then their ordered sum into Cf
         hipLaunchKernelGGL((k_gemm<TA, TB, EPI>), grid, dim3(256), 0, s, A, B, M, N, K, lda, ldb, bias,
-                           mask, ldm, part, Cb, N);
+                           part, Cb, N);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         const int64_t n = (int64_t)M * N;
@@ -210,7 +208,7 @@ hipError_t gemm(const uint16_t *A, const uint16_t *B, int M, int N, int K, int l
         return hipGetLastError();
     }
     hipLaunchKernelGGL((k_gemm<TA, TB, EPI>), grid, dim3(256), 0, s, A, B, M, N, K, lda, ldb, bias,
-                       mask, ldm, Cf, Cb, ldc);
+                       Cf, Cb, ldc);
     return hipGetLastError();
 }
 
@@ -243,9 +241,7 @@ hipError_t mlp_gemm(int variant, const uint16_t *A, const uint16_t *B, int M, in
     }
     switch (variant) {
     case kGemmFwd:    // Y = X W^T (+ b, ReLU, BF16)
-        return gemm<false, true, kEpiBiasReluBf16>(A, B, M, N, K, lda, ldb, bias, mask, ldm, Cf, Cb, ldc, s);
-    case kGemmDx:     // dpre_prev = mask(dY W)
-        return gemm<false, false, kEpiMaskBf16>(A, B, M, N, K, lda, ldb, bias, mask, ldm, Cf, Cb, ldc, s);
+        return gemm<false, true, kEpiBiasReluBf16>(A, B, M, N, K, lda, ldb, bias, Cf, Cb, ldc, s);
     case kGemmDw: {   // dW = dY^T X, split over the rows (K) into the workspace when given
         const int tiles = ((N + kBN - 1) / kBN) * ((M + kBM - 1) / kBM);
         int splits = 1;
@@ -257,16 +253,15 @@ hipError_t mlp_gemm(int variant, const uint16_t *A, const uint16_t *B, int M, in
             splits = splits > kMaxDwSplits ? kMaxDwSplits : splits;
             if (splits < 1) splits = 1;
         }
-        return gemm<true, false, kEpiF32>(A, B, M, N, K, lda, ldb, bias, mask, ldm, Cf, Cb, ldc, s,
-                                          splits, ws);
+        return gemm<true, false, kEpiF32>(A, B, M, N, K, lda, ldb, bias, Cf, Cb, ldc, s, splits, ws);
     }
     case kGemmNtF32:  // plain C = A B^T in FP32 (tests)
-        return gemm<false, true, kEpiF32>(A, B, M, N, K, lda, ldb, bias, mask, ldm, Cf, Cb, ldc, s);
+        return gemm<false, true, kEpiF32>(A, B, M, N, K, lda, ldb, bias, Cf, Cb, ldc, s);
     case kGemmNnF32:
-        return gemm<false, false, kEpiF32>(A, B, M, N, K, lda, ldb, bias, mask, ldm, Cf, Cb, ldc, s);
+        return gemm<false, false, kEpiF32>(A, B, M, N, K, lda, ldb, bias, Cf, Cb, ldc, s);
     case kGemmTnF32:
-        return gemm<true, false, kEpiF32>(A, B, M, N, K, lda, ldb, bias, mask, ldm, Cf, Cb, ldc, s);
-    default:
+        return gemm<true, false, kEpiF32>(A, B, M, N, K, lda, ldb, bias, Cf, Cb, ldc, s);
+    default:          // (kGemmDx: the tiled kernel's only)
         return hipErrorInvalidValue;
     }
 }
@@ -276,12 +271,9 @@ hipError_t mlp_gemm_parts(const uint16_t *A, const uint16_t *B, int M, int N, in
 {
     if (M <= 0 || N <= 0) return hipSuccess;
     if (splits < 1 || !part) return hipErrorInvalidValue;
-    if (gemm_tiles_fit(false, false, A, B, M, N, K, lda, ldb, nullptr, nullptr, 0, part, N))
-        return gemm_tiles(kGemmNtF32, A, B, M, N, K, lda, ldb, nullptr, nullptr, 0, part, nullptr, N, splits, s);
-    const dim3 grid((N + kBN - 1) / kBN, (M + kBM - 1) / kBM, splits);
-    hipLaunchKernelGGL((k_gemm<false, true, kEpiF32>), grid, dim3(256), 0, s, A, B, M, N, K, lda, ldb, nullptr,
-                       nullptr, 0, part, nullptr, N);
-    return hipGetLastError();
+    if (!gemm_tiles_fit(false, false, A, B, M, N, K, lda, ldb, nullptr, nullptr, 0, part, N))
+        return hipErrorInvalidValue;
+    return gemm_tiles(kGemmNtF32, A, B, M, N, K, lda, ldb, nullptr, nullptr, 0, part, nullptr, N, splits, s);
 }
 
 hipError_t mlp_adam(float *w, float *m, float *v, const float *g, int64_t n, float lr, float b1,
