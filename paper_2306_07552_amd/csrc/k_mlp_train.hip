@@ -285,8 +285,9 @@ hipError_t mlp_mid_layout(const uint16_t *w1, const uint16_t *w2, const uint16_t
 hipError_t mlp_mid(const MlpMidArgs &a, int *slabs, hipStream_t s)
 {
     if (a.rows <= 0) return hipErrorInvalidValue;
-    // 16 rows per workgroup up to one workgroup per CU, then 32 (the whole gradient
-    // of 4096 rows: 53 us with 16, 57 with 32)
+    // 16 rows per workgroup up to one workgroup per CU, then 32, which halve the
+    // weights streamed per row.  The whole gradient with 16 and 32, us: 1024 rows
+    // 41.3 and 45.4, 4096 49.4 and 52.9, 4112 61.5 and 54.7, 8192 71.9 and 62.7.
     const int R = a.rows <= 16 * 256 ? 16 : 32;
     const int grid = std::min((a.rows + R - 1) / R, kMidGrid);
     *slabs = grid;
