@@ -448,10 +448,10 @@ def main():
                            "sq_insts_valu_per_launch": valu}
     else:
         roofline["alu"] = None
-    if roofline["alu"] and roofline["alu"]["frac"] > roofline["frac"]:
-        roofline["binding"] = "alu"
-    else:
-        roofline["binding"] = "hbm"
+    # what binds the kernel: the counted traffic where there is a record (most of the
+    # algorithmic bytes belong to culled clusters, which are never read)
+    hbm_frac = (traffic / raster_bytes if traffic else 1.0) * roofline["frac"]
+    roofline["binding"] = "alu" if roofline["alu"] and roofline["alu"]["frac"] > hbm_frac else "hbm"
     if sur:
         flop = N * SURROGATE_FLOP_PER_ROW
         roofline["surrogate"] = {

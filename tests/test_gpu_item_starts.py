@@ -95,3 +95,28 @@ def test_ordering_is_hidden_beside_the_robot_step(n, lanes):
                 best[order] = min(best[order], robot)
     print("robot stage, ms: static %.4f, by time %.4f" % tuple(best), flush=True)
     assert best[1] - best[0] < 0.015
+
+
+@pytest.mark.parametrize("n,items", [(513, 8208), (2048, 32768), (2049, 32784)])
+def test_items_by_the_ten_thousand(n, items):
+    """More items than the sort keeps in registers, its largest count, and one env
+    more, which keeps the static order."""
+    import torch
+    from paper_2306_07552_amd import gal
+    print("case: items by the ten thousand", n, flush=True)
+    cfg = sg.scaled_config(0, n)
+    scenes = sg.make_scene_set(cfg)
+    scenes.res = np.full(n, 128, np.int32)
+    robot, consts = sg.make_robot_for(cfg), sg.config_constants(cfg)
+    b, ref = gal.Batch(robot, scenes, consts), gal.Batch(robot, scenes, consts)
+    b.set_tuning(region=32)
+    info = b.launch_info()
+    assert info["items"] == items and info["by_time"] == (items <= 32768)
+    out, want = b.alloc_outputs(), ref.alloc_outputs()
+    for k in range(3):
+        acts = torch.from_numpy(sg.actions(cfg, k, num_envs=n)).cuda()
+        b.step(acts, out)
+        ref.step(acts, want)
+        torch.cuda.synchronize()
+        for name in want:
+            assert torch.equal(out[name], want[name]), (k, name)
