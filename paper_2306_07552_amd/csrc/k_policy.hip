@@ -183,7 +183,7 @@ __global__ __launch_bounds__(256) void k_policy_heads(FcParts fc, uint16_t *__re
 // out[i] = sum over splits of part[z][i].  A workgroup sums 64 outputs, its
 // wave w the splits w, w + 4, ... in order, then the four waves' sums in order:
 // with one thread per output, a gradient of 35 thousand values in 256 slabs kept
-// half the chip's CUs on chains of 256 dependent loads (65 us; 10 us like this).
+// half the chip's CUs on chains of 256 dependent loads (65 us; 7 us like this).
 __global__ __launch_bounds__(256) void k_sum_parts(const float *__restrict__ part, int splits, int64_t n,
                                                    float *__restrict__ out)
 {

@@ -3,13 +3,15 @@
 // and input gradient), then the second (both) with the first layer's weight
 // gradient.  The first layer's output gradient never leaves LDS.
 //
-// What bounds them: memory traffic (59 KB per sample for the third layer, 150
-// KB for the second and first), LDS reads and matrix work close behind, with
-// two waves per SIMD to overlap them.  As one kernel per layer and gradient, the
-// largest map (61.5 KB per sample) crossed memory six times, its gradient
-// included, and each input pixel was gathered once per tap.  Measured, 32,768
-// samples: 2.7 -> 0.60 ms for the third layer (3.2 TB/s), 9.5 -> 1.65 ms for
-// the second and first (3.0 TB/s).
+// What bounds them: no one unit.  Of the time of 32,768 samples memory moves 59 KB
+// per sample for the third layer and 153 KB for the second and first (3.2 and 3.0
+// of 4.7 TB/s), the LDS is busy for 0.39 and 0.30, the matrix cores for 0.30 and
+// 0.29, VALU issue for 0.37 and 0.33; two waves per SIMD and a barrier per phase
+// overlap these only in part (waves wait 0.46 and 0.37 of their cycles).  As one
+// kernel per layer and gradient, the largest map (61.5 KB per sample) crossed memory
+// six times, its gradient included, and each input pixel was gathered once per tap.
+// Measured, 32,768 samples: 2.7 -> 0.60 ms for the third layer, 9.5 -> 1.65 ms for
+// the second and first.
 //
 // A weight gradient is dY^T times the windows of the input, summed over the
 // output pixels: both operands lie in LDS pixel by pixel, so their fragments
