@@ -304,7 +304,9 @@ int gal_step(gal_batch *b, const float *actions_dev, const gal_outputs *out, voi
  *             per wave) or 32 (two envs per wave)
  *  graph      1 = gal_step replays the whole step as a captured hipGraph
  *             (re-captured when the action/output pointers or the tuning
- *             change; not used while gal_profile is enabled)
+ *             change; not used while gal_profile is enabled); it spares the
+ *             host the launches, while the GPU takes 6-7 us a step more than
+ *             with launches that are queued ahead
  *  split      number of envs (0..N), taken from the cheap end of the
  *             longest-first item order, whose regions are halved (four
  *             items per region instead of one) so that the last items of a
@@ -390,7 +392,7 @@ int gal_project_test(const float *x_dev, const float *z_dev, int64_t n, float *q
  * winner (3 x `steps` each, three interleaved rounds).  It
  * checks that every candidate produces the same depth bits from the same
  * state, keeps the fastest (also written to *best, with its time per step in
- * *best_ms) and restores the simulation state it started from.  The outputs'
+ * *best_ms; graph stays as it was, the candidates are timed without) and restores the simulation state it started from.  The outputs'
  * contents are overwritten.  Synchronous.  GAL_ESTATE if a candidate's output
  * differs.
  */

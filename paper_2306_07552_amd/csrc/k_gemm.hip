@@ -6,10 +6,11 @@
 // or k-strided (rows of m or n, one per k).  K advances 64 at a time through a
 // ring of LDS stages filled straight from memory (global_load_lds, no
 // registers), one barrier per stage; a k-strided operand's fragments come from
-// the transposing LDS read.  What bounds it: what reaches LDS from L2, 12 TB/s
-// over the chip on large products (2.4 GB in 199 us for C 32768 x 512, K 4608, where
-// the matrix cores are busy for 0.31 of the time and the LDS for 0.16), the latency
-// of the stages in flight on small ones; measured at the tile rule below.
+// the transposing LDS read.  What bounds it: what reaches LDS on large products,
+// 10-13 TB/s from L2 over the chip (C 32768 x 512, K 4608: 2.4 GB in 199 us, the
+// matrix cores busy for 0.31 of the time, the LDS for 0.15), of which the products
+// with the largest operands take 5.2 TB/s from memory; the latency of the stages in
+// flight on small ones; measured at the tile rule below.
 //
 // Sums run over ascending 32-wide steps of k in FP32, so results do not depend
 // on the tile shape.
